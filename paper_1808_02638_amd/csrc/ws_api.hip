@@ -246,6 +246,8 @@ struct ws_ctx {
   std::vector<PatchRow> rows;
   std::vector<TileEntry> tiles;
   std::vector<PackWave> packs;  // wavefronts of the PACKED tiles
+  std::vector<TileEntry> two_tiles;  // tiles of the two-step launch (empty: it does not apply)
+  int two_rows = 0;                  // rows per segment of theirs
   std::vector<TileEntry> stiles;  // conservation-sum tiles (fixed by the patch sizes)
   std::vector<int> order;  // patches largest first
   int n_cu = 0, wg_per_cu = 0, grid = 0, occupancy = 0;
@@ -263,6 +265,7 @@ struct ws_ctx {
   hipGraphExec_t gexec = nullptr;
   int graph_steps = 0, graph_start_pool = 0;
   std::vector<InstRow> inst_host;  // (c, Z) per instance, as on the device
+  std::vector<InstMin> min_host;   // smallest cell sizes per instance
   void *medium = nullptr;          // per-cell (c, Z) planes, laid out like a q pool
   // tiled level: per-patch ghost-ring offsets and the ghost source table
   const int64_t *link_ring0 = nullptr;
@@ -272,9 +275,20 @@ struct ws_ctx {
   // limiter code of the kernel launchers (the medium selects its own kernel)
   int lim_code() const { return limiter | (medium ? kMediumFlag : 0); }
 
-  CflSlots slots() {
+  // Time step per instance of the state in pool `which`.  A homogeneous
+  // step reads its source pool's slot and writes the other one; the second
+  // slot and the smallest cell sizes per instance take the place of a
+  // medium's accumulators, which such a level does not have.
+  double *dt_slot(int which) {
+    return reinterpret_cast<double *>(ws + (which == 0 || medium ? L.dt : L.inst_acc));
+  }
+  InstMin *inst_min() { return reinterpret_cast<InstMin *>(ws + L.inst_acc + 8LL * n_inst); }
+
+  // Bookkeeping of a step that leaves its state in pool `dst`.
+  CflSlots slots(int dst) {
     CflSlots c;
-    c.dt = reinterpret_cast<double *>(ws + L.dt);
+    c.dt = dt_slot(dst);
+    c.inst_min = inst_min();
     c.cfl_tile = reinterpret_cast<double *>(ws + L.cfl_tile);
     c.inst_acc = reinterpret_cast<unsigned long long *>(ws + L.inst_acc);
     c.cfl_last = reinterpret_cast<double *>(ws + L.cfl_last);
@@ -298,8 +312,8 @@ struct ws_ctx {
     a.qout = pool[1 - src];
     a.pool_bytes = (int32_t)std::min<int64_t>(pool_bytes, INT32_MAX);
     a.inst = reinterpret_cast<const InstRow *>(ws + L.inst);
-    a.slots = slots();
-    a.dt = a.slots.dt;
+    a.slots = slots(1 - src);
+    a.dt = dt_slot(src);
     a.dt_override = dt_override;
     a.cfl_desired = cfl_desired;
     a.retire = reinterpret_cast<unsigned int *>(ws + L.retire);
@@ -321,6 +335,31 @@ struct ws_ctx {
     if ((int64_t)packs.size() > L.max_pack_waves)
       return fail(WS_EINVAL, "PACKED wavefront list overflow");
     return WS_OK;
+  }
+
+  // Tiles of the two-step launch of captured loops, after the step's own in
+  // the tile list, where the level takes one and they fit.
+  void build_two_tiles() {
+    two_tiles.clear();
+    if (medium || (limiter & WS_TRANSVERSE_CORR)) return;
+    for (const PatchRow &r : rows)
+      if (r.bc != WS_BC_EXTRAP || !march_fits(r.plane, dtype)) return;
+    auto count = [&](int seg) {
+      int64_t n = 0;
+      for (const PatchRow &r : rows) n += ceil_div(r.mx, kMultiCols) * ceil_div(r.my, 4 * seg);
+      return n;
+    };
+    two_rows = 4;
+    while (two_rows < kMaxMarchRows && count(two_rows) > 2 * (int64_t)n_cu) ++two_rows;
+    if (const char *e = getenv("WS_TWO_ROWS")) two_rows = atoi(e);
+    if ((int64_t)tiles.size() + count(two_rows) > L.max_tiles) return;
+    for (int k : order) {
+      const PatchRow &r = rows[k];
+      const int ntx = (int)ceil_div(r.mx, kMultiCols), nty = (int)ceil_div(r.my, 4 * two_rows);
+      for (int ty = 0; ty < nty; ++ty)
+        for (int tx = 0; tx < ntx; ++tx)
+          two_tiles.push_back(TileEntry{k, (uint16_t)tx, (uint16_t)ty});
+    }
   }
 
   // Tile list: patches largest first, each patch's tiles row by row; then the
@@ -348,6 +387,10 @@ struct ws_ctx {
                           hipMemcpyHostToDevice, stream));
     HIPCHK(hipMemcpyAsync(ws + L.tiles, tiles.data(), tiles.size() * sizeof(TileEntry),
                           hipMemcpyHostToDevice, stream));
+    build_two_tiles();
+    if (!two_tiles.empty())
+      HIPCHK(hipMemcpyAsync(ws + L.tiles + tiles.size() * sizeof(TileEntry), two_tiles.data(),
+                            two_tiles.size() * sizeof(TileEntry), hipMemcpyHostToDevice, stream));
     if (!packs.empty())
       HIPCHK(hipMemcpyAsync(ws + L.packs, packs.data(), packs.size() * sizeof(PackWave),
                             hipMemcpyHostToDevice, stream));
@@ -426,6 +469,12 @@ static int setup_level(ws_ctx *c, const ws_patch_desc *patches, int32_t n_patche
     inst[k].Z = mats[k].rho * inst[k].c;
   }
   c->inst_host = inst;
+  c->min_host.assign(n_instances, InstMin{HUGE_VAL, HUGE_VAL});
+  for (int k = 0; k < n_patches; ++k) {
+    InstMin &m = c->min_host[patches[k].instance];
+    m.dx = std::min(m.dx, patches[k].dx);
+    m.dy = std::min(m.dy, patches[k].dy);
+  }
   c->rows.resize(n_patches);
   int64_t mask_off = 0;
   for (int k = 0; k < n_patches; ++k) {
@@ -503,6 +552,9 @@ int ws_init_patches(ws_ctx **out, const ws_patch_desc *patches, int32_t n_patche
   if (hipMemcpyAsync(c->ws + c->L.inst, inst.data(), inst.size() * sizeof(InstRow),
                      hipMemcpyHostToDevice, c->stream) != hipSuccess)
     return bail(fail(WS_EHIP, "uploading the instance table failed"));
+  if (hipMemcpyAsync(c->inst_min(), c->min_host.data(), c->min_host.size() * sizeof(InstMin),
+                     hipMemcpyHostToDevice, c->stream) != hipSuccess)
+    return bail(fail(WS_EHIP, "uploading the cell sizes failed"));
   if (int rc = c->build_tiles()) return bail(rc);
   *out = c;
   return WS_OK;
@@ -556,6 +608,14 @@ int ws_attach_medium(ws_ctx *c, void *medium, int64_t bytes) {
     if (3 * c->rows[k].plane * es >= ((int64_t)1 << 32))
       return fail(WS_EINVAL, "patch %d: its three planes span 4 GiB or more (too large for a "
                   "heterogeneous medium)", k);
+  if (!c->medium) {
+    // a medium keeps one time-step slot, and accumulators that start at zero
+    // in the place of the second
+    if (c->cur == 1)
+      HIPCHK(hipMemcpyAsync(c->dt_slot(0), c->dt_slot(1), 8 * (size_t)c->n_inst,
+                            hipMemcpyDeviceToDevice, c->stream));
+    HIPCHK(hipMemsetAsync(c->ws + c->L.inst_acc, 0, 8 * (size_t)kGroups * c->n_inst, c->stream));
+  }
   HIPCHK(hipStreamSynchronize(c->stream));
   c->medium = medium;
   // DIRECT tiles (the default DIRECT shape of each patch)
@@ -792,14 +852,13 @@ int ws_step_level_per_patch(ws_ctx *c, double dt, double *cfl_out) {
   if (!c) return fail(WS_EINVAL, "ctx is NULL");
   if (c->vars & 4) return fail(WS_EINVAL, "per-patch launches need a tiling without PACKED tiles");
   if (!(dt > 0.0) || !std::isfinite(dt)) return fail(WS_EINVAL, "dt must be finite and > 0");
-  HIPCHK(launch_set_dt(c->slots(), dt, c->stream));
-  StepArgs a = c->step_args(c->cur, 0.0, 0.0);
+  StepArgs a = c->step_args(c->cur, dt, 0.0);
   a.persistent = 0;
   for (int k : c->order) {  // largest patch first
     a.tile_base = c->rows[k].tile_begin;
     HIPCHK(launch_step(c->dtype, c->lim_code(), c->vars, a, c->rows[k].n_tiles, c->stream));
   }
-  HIPCHK(launch_finish_step(c->slots(), 0.0, c->stream));
+  HIPCHK(launch_finish_step(a, c->stream));
   if (int rc = link_after_step(c, 1 - c->cur)) return rc;
   c->cur = 1 - c->cur;
   return read_level_cfl(c, cfl_out);
@@ -813,7 +872,7 @@ int ws_set_dt(ws_ctx *c, const double *dt_per_instance) {
       return fail(WS_EINVAL, "dt[%d] must be finite and > 0", k);
   HIPCHK(hipStreamSynchronize(c->stream));
   std::memcpy(c->host_buf, dt_per_instance, 8 * (size_t)c->n_inst);
-  HIPCHK(hipMemcpyAsync(c->ws + c->L.dt, c->host_buf, 8 * (size_t)c->n_inst,
+  HIPCHK(hipMemcpyAsync(c->dt_slot(c->cur), c->host_buf, 8 * (size_t)c->n_inst,
                         hipMemcpyHostToDevice, c->stream));
   HIPCHK(hipMemsetAsync(c->ws + c->L.cfl_max, 0, 8 * (size_t)c->n_inst, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
@@ -824,6 +883,16 @@ static int enqueue_auto(ws_ctx *c, int src, double cfl_desired) {
   StepArgs a = c->step_args(src, 0.0, cfl_desired);
   HIPCHK(launch_step(c->dtype, c->lim_code(), c->vars, a, c->grid, c->stream));
   return link_after_step(c, 1 - src);
+}
+
+// Two steps in one launch, from pool `src` into the other.
+static int enqueue_two(ws_ctx *c, int src, double cfl_desired) {
+  StepArgs a = c->step_args(src, 0.0, cfl_desired);
+  a.tiles = c->d_tiles() + c->tiles.size();
+  a.n_tiles = (int32_t)c->two_tiles.size();
+  a.seg_rows = c->two_rows;
+  HIPCHK(launch_step_two(c->dtype, c->limiter, a, c->stream));
+  return WS_OK;
 }
 
 int ws_step_auto(ws_ctx *c, double cfl_desired) {
@@ -844,7 +913,17 @@ int ws_capture_steps(ws_ctx *c, int32_t n_steps, double cfl_desired) {
   HIPCHK(hipStreamSynchronize(c->stream));
   HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
   int rc = WS_OK;
-  for (int s = 0; s < n_steps && rc == WS_OK; ++s) rc = enqueue_auto(c, (c->cur + s) & 1, cfl_desired);
+  // Pairs of steps in one launch where the level takes them.  Their number is
+  // even, so that the state ends in the pool (and its time-step slot) that
+  // n_steps single steps leave it in, and the last step is a single one, so
+  // that the other pool holds the state before it and every reported Courant
+  // number is that step's.
+  const int pairs = c->two_tiles.empty() || c->link_src ? 0 : (n_steps - 1) / 4 * 2;
+  int src = c->cur;
+  for (int s = 0; s < pairs && rc == WS_OK; ++s, src = 1 - src)
+    rc = enqueue_two(c, src, cfl_desired);
+  for (int s = 2 * pairs; s < n_steps && rc == WS_OK; ++s, src = 1 - src)
+    rc = enqueue_auto(c, src, cfl_desired);
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(c->stream, &g);
   if (rc != WS_OK) {
@@ -873,7 +952,7 @@ int ws_read_dt_cfl(ws_ctx *c, double *dt, double *cfl_last, double *cfl_max) {
   if (!c) return fail(WS_EINVAL, "ctx is NULL");
   const size_t n = 8 * (size_t)c->n_inst;
   double *h = c->host_buf;
-  HIPCHK(hipMemcpyAsync(h, c->ws + c->L.dt, n, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(hipMemcpyAsync(h, c->dt_slot(c->cur), n, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipMemcpyAsync(h + c->n_inst, c->ws + c->L.cfl_last, n, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipMemcpyAsync(h + 2 * c->n_inst, c->ws + c->L.cfl_max, n, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
@@ -887,7 +966,7 @@ int ws_read_patch_cfl(ws_ctx *c, double *cfl) {
   if (!c) return fail(WS_EINVAL, "ctx is NULL");
   if (!cfl) return fail(WS_EINVAL, "cfl is NULL");
   double *dpatch = reinterpret_cast<double *>(c->ws + c->L.cfl_patch_last);
-  HIPCHK(launch_patch_cfl(c->d_patches(), c->n_patches, c->slots().cfl_tile, dpatch, c->stream));
+  HIPCHK(launch_patch_cfl(c->d_patches(), c->n_patches, c->slots(0).cfl_tile, dpatch, c->stream));
   const size_t n = 8 * (size_t)c->n_patches;
   HIPCHK(hipMemcpyAsync(c->host_buf, dpatch, n, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
@@ -935,8 +1014,8 @@ int ws_time_step_kernel(ws_ctx *c, int32_t n_launches, int32_t per_patch, double
         e = launch_step(c->dtype, c->lim_code(), c->vars, a, c->rows[k].n_tiles, c->stream);
         if (e != hipSuccess) break;
       }
-      // per-patch launches leave their Courant numbers in the accumulators
-      if (e == hipSuccess) e = launch_finish_step(c->slots(), 0.0, c->stream);
+      // per-patch launches file no Courant numbers
+      if (e == hipSuccess) e = launch_finish_step(a, c->stream);
     } else if (e == hipSuccess) {
       e = launch_step(c->dtype, c->lim_code(), c->vars, a, c->grid, c->stream);
     }
@@ -1121,6 +1200,8 @@ int ws_step_level_noalloc(const ws_patch_desc *patches, int32_t n_patches,
   // must start at zero (accumulators, retirement counters), then the tables
   HIPCHK(hipMemsetAsync(ws + c.L.dt, 0, c.L.partials - c.L.dt, c.stream));
   HIPCHK(hipMemcpyAsync(ws + c.L.inst, c.inst_host.data(), c.inst_host.size() * sizeof(InstRow),
+                        hipMemcpyHostToDevice, c.stream));
+  HIPCHK(hipMemcpyAsync(c.inst_min(), c.min_host.data(), c.min_host.size() * sizeof(InstMin),
                         hipMemcpyHostToDevice, c.stream));
   if (int rc = c.build_tiles()) return rc;  // uploads the tables, synchronises
   StepArgs a = c.step_args(0, dt, 0.0);

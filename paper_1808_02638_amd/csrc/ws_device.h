@@ -149,4 +149,38 @@ __device__ inline void gtilde(const Coef<T> &k, T b1, T b2, T b1_up, T b2_down, 
   gtilde_l<T>(k, limited<T, LIM>(b1, b1_up), limited<T, LIM>(b2, b2_down), xs_lo, xs_hi, Gp, Gv);
 }
 
+// Flux-differencing update of one cell, eq. (2.3).
+template <typename T>
+__device__ inline void update(const Coef<T> &k, T p0, T u0, T v0, T xs0, T xd0, T ys0, T yd0,
+                              T FLp, T FLu, T FRp, T FRu, T GBp, T GBv, T GTp, T GTv, T &pn, T &un,
+                              T &vn) {
+  pn = p0 - k.dtdx * (k.h * xs0 + (FRp - FLp)) - k.dtdy * (k.h * ys0 + (GTp - GBp));
+  un = u0 - k.dtdx * (k.hz * xd0 + (FRu - FLu));
+  vn = v0 - k.dtdy * (k.hz * yd0 + (GTv - GBv));
+}
+
+// Raw buffer stores (gfx9 buffer resource, no format conversion).  An offset
+// at or past the resource's size is dropped by the hardware.  The stores are
+// device-scope (cache policy SC1: written through the XCD's L2), so the L2s
+// hold no dirty output to write back when the launch ends; the next step's
+// workgroups read it on whichever XCD they run.
+constexpr int kRawBufferWord3 = 0x00020000;
+constexpr unsigned kDropOffset = 0x80000000u;
+constexpr int kStoreDeviceScope = 16;  // SC1
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+__device__ inline void bstore(__amdgpu_buffer_rsrc_t r, double v, unsigned off) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0,
+                                        kStoreDeviceScope);
+}
+__device__ inline void bstore(__amdgpu_buffer_rsrc_t r, float v, unsigned off) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0,
+                                        kStoreDeviceScope);
+}
+
+// One row of (p, u, v) of a MARCH segment's column.
+template <typename T>
+struct Row3 {
+  T p, u, v;
+};
+
 }  // namespace ws

@@ -9,11 +9,17 @@
 
 namespace ws {
 
+// Smallest cell sizes over an instance's patches (infinite: it has none).
+struct InstMin {
+  double dx, dy;
+};
+
 // Per-step Courant-number bookkeeping inside the workspace.
 struct CflSlots {
-  double *dt;                    // [n_inst]
+  double *dt;                    // [n_inst] the time step the step leaves behind
+  const InstMin *inst_min;       // [n_inst] (homogeneous levels)
   double *cfl_tile;              // [n_tiles] Courant number of each tile of the step
-  unsigned long long *inst_acc;  // [kGroups][n_inst] per-XCD-group maxima (FP64 bits)
+  unsigned long long *inst_acc;  // [kGroups][n_inst] per-XCD-group maxima (FP64 bits; a medium only)
   double *cfl_last;              // [n_inst]  Courant number of the last step
   double *cfl_max;               // [n_inst]  largest since ws_set_dt
   double *level_last;            // [1]
@@ -31,13 +37,14 @@ struct StepArgs {
   void *qout;
   int32_t pool_bytes;  // bytes of each pool (PACKED tiles: below 2^31)
   const InstRow *inst;
-  double *dt;          // per instance
+  const double *dt;    // per instance, read by every tile
   double dt_override;  // > 0: every instance steps with this dt (stored into dt)
   double cfl_desired;  // > 0: after the step, dt <- dt * cfl_desired / cfl
   CflSlots slots;
   unsigned int *retire;  // (kGroups + 1) counters, kLine apart
   uint8_t *masks;        // nullptr unless the branches are recorded
   const void *medium;    // nullptr, or per-cell (c, Z) planes laid out like a q pool
+  int32_t seg_rows;      // two-step launch: rows per segment
 };
 
 // Bit OR-ed into the limiter code of the kernel launchers when the level has a
@@ -49,6 +56,11 @@ constexpr int kMediumFlag = 0x10000;
 // PACKED tiles present.
 hipError_t launch_step(int dtype, int limiter, int vars, const StepArgs &a, int grid,
                        hipStream_t s);
+// Two steps in one launch (ws_multi.hip): homogeneous levels whose patches all
+// have extrapolation boundaries, default transverse variant; a.tiles are
+// kMultiCols columns by 4 seg_rows rows, a.cfl_desired > 0 rescales dt after
+// each of the two steps.
+hipError_t launch_step_two(int dtype, int limiter, const StepArgs &a, hipStream_t s);
 // The ghost ring of an mx x my patch in one numbering, shared by the kernels
 // that walk it and the host tables indexed by it: rows -2, -1 across the
 // padded width, rows my, my+1, then columns -2, -1, mx, mx+1 of the interior
@@ -74,12 +86,9 @@ hipError_t launch_link_ghosts(int dtype, const PatchRow *patches, int n_patches,
 
 hipError_t launch_fill_ghosts(int dtype, const PatchRow *patches, int n_patches,
                               int max_padded_cells, void *q, hipStream_t s);
-// dt[k] = value for every instance.
-hipError_t launch_set_dt(const CflSlots &c, double value, hipStream_t s);
-// Move the step's accumulated Courant numbers to the *_last slots, update the
-// running maxima, clear the accumulators and, if cfl_desired > 0, rescale
-// each instance's dt by cfl_desired / cfl.
-hipError_t launch_finish_step(const CflSlots &c, double cfl_desired, hipStream_t s);
+// File a step's Courant numbers where no step kernel did (per-patch
+// launches): with a medium from the accumulators, else from the closed form.
+hipError_t launch_finish_step(const StepArgs &a, hipStream_t s);
 // cfl_patch[k] = max of cfl_tile over patch k's tiles.
 hipError_t launch_patch_cfl(const PatchRow *patches, int n_patches, const double *cfl_tile,
                             double *cfl_patch, hipStream_t s);

@@ -69,16 +69,6 @@ __device__ inline T moved(T xs, T t, T d_lo, T d_hi) {
   return xs + t * (d_hi - d_lo);
 }
 
-// Flux-differencing update of one cell, eq. (2.3).
-template <typename T>
-__device__ inline void update(const Coef<T> &k, T p0, T u0, T v0, T xs0, T xd0, T ys0, T yd0,
-                              T FLp, T FLu, T FRp, T FRu, T GBp, T GBv, T GTp, T GTv, T &pn, T &un,
-                              T &vn) {
-  pn = p0 - k.dtdx * (k.h * xs0 + (FRp - FLp)) - k.dtdy * (k.h * ys0 + (GTp - GBp));
-  un = u0 - k.dtdx * (k.hz * xd0 + (FRu - FLu));
-  vn = v0 - k.dtdy * (k.hz * yd0 + (GTv - GBv));
-}
-
 // Padded planes of one patch, indexed by interior coordinates (i, j).
 template <typename T>
 struct Planes {
@@ -608,37 +598,12 @@ __device__ inline T march_col_var(const Planes32<T> &q, const Planes32<T> &md, i
 }
 
 
-// Raw buffer stores (gfx9 buffer resource, no format conversion).  An offset
-// at or past the resource's size is dropped by the hardware.  The stores are
-// device-scope (cache policy SC1: written through the XCD's L2), so the L2s
-// hold no dirty output to write back when the launch ends; the next step's
-// workgroups read it on whichever XCD they run.
-constexpr int kRawBufferWord3 = 0x00020000;
-constexpr unsigned kDropOffset = 0x80000000u;
-constexpr int kStoreDeviceScope = 16;  // SC1
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-__device__ inline void bstore(__amdgpu_buffer_rsrc_t r, double v, unsigned off) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0,
-                                        kStoreDeviceScope);
-}
-__device__ inline void bstore(__amdgpu_buffer_rsrc_t r, float v, unsigned off) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0,
-                                        kStoreDeviceScope);
-}
-
 // s_waitcnt immediate (gfx9 encoding) waiting for vmcnt(0) only.
 constexpr int kWaitVmcnt0 = 0x0F70;
 
 // Row sets of a MARCH segment (its row loop is unrolled by this count and
 // names eight sets).
 constexpr int kSets = 8;
-
-// One row of (p, u, v) of a MARCH segment's column.
-template <typename T>
-struct Row3 {
-  T p, u, v;
-};
-
 
 // Lanes of one MARCH segment (one wavefront, w = 64 lanes): lane l holds
 // column i = c0-2+l, the segment updates columns c0..c0+w-5 (lanes 2..w-3)
@@ -1432,16 +1397,29 @@ __device__ inline unsigned long long load_agent(const unsigned long long *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// File the step's Courant numbers: per instance the max over the XCD groups'
-// accumulators (which are cleared), the level max, running maxima, and dt set
-// (dt_override > 0) and rescaled by cfl_desired / cfl (cfl_desired > 0),
-// Sec. 2.5 eq. (2.11).  Run by one whole workgroup after every tile of the
-// step has finished.
-__device__ inline void finish_step(const CflSlots &c, double dt_override, double cfl_desired) {
+// The level maximum of a workgroup's per-thread Courant numbers.
+__device__ inline void file_level(double lvl, double *out) {
   __shared__ double s_lvl[kThreads / 64];
   const int tid = (int)threadIdx.x;
+  lvl = wave_max(lvl);
+  if ((tid & 63) == 0) s_lvl[tid >> 6] = lvl;
+  __syncthreads();
+  if (tid == 0) {
+    double m = s_lvl[0];
+    for (int w = 1; w < kThreads / 64; ++w) m = fmax(m, s_lvl[w]);
+    out[0] = m;
+  }
+}
+
+// File the Courant numbers of a step in a medium: per instance the max over
+// the XCD groups' accumulators (which are cleared), the level max, running
+// maxima, and dt set (dt_override > 0) and rescaled by cfl_desired / cfl
+// (cfl_desired > 0), Sec. 2.5 eq. (2.11).  Run by one whole workgroup after
+// every tile of the step has finished.
+__device__ inline void finish_step(const CflSlots &c, const double *dt_in, double dt_override,
+                                   double cfl_desired) {
   double lvl = 0.0;
-  for (int k = tid; k < c.n_inst; k += kThreads) {
+  for (int k = (int)threadIdx.x; k < c.n_inst; k += kThreads) {
     unsigned long long b = 0;
     for (int g = 0; g < kGroups; ++g) {
       unsigned long long *slot = &c.inst_acc[(int64_t)g * c.n_inst + k];
@@ -1451,23 +1429,42 @@ __device__ inline void finish_step(const CflSlots &c, double dt_override, double
     const double cfl = __longlong_as_double((long long)b);
     c.cfl_last[k] = cfl;
     c.cfl_max[k] = fmax(c.cfl_max[k], cfl);
-    double dt = dt_override > 0.0 ? dt_override : c.dt[k];
+    double dt = dt_override > 0.0 ? dt_override : dt_in[k];
     if (cfl_desired > 0.0 && cfl > 0.0) dt = dt * cfl_desired / cfl;
     c.dt[k] = dt;
     lvl = fmax(lvl, cfl);
   }
-  lvl = wave_max(lvl);
-  if ((tid & 63) == 0) s_lvl[tid >> 6] = lvl;
-  __syncthreads();
-  if (tid == 0) {
-    double m = s_lvl[0];
-    for (int w = 1; w < kThreads / 64; ++w) m = fmax(m, s_lvl[w]);
-    c.level_last[0] = m;
-  }
+  file_level(lvl, c.level_last);
 }
 
-// A workgroup's running maximum over consecutive tiles of one instance, filed
-// into its XCD group's slot with one atomic max per run.  The atomic returns
+// The same for a homogeneous level, whose Courant numbers need no reduction:
+// every edge of an instance carries the speeds -c, 0, +c, so its largest
+// s dt/dx is c dt over its smallest cell size (division and multiplication
+// round monotonically, so this is bitwise the maximum over its patches).  dt
+// is read from one slot and written to another (the slots change places with
+// the state's pools), so one workgroup files this while the others still
+// read the old dt: no tile waits for another, and the step has no reduction,
+// no atomics and no last workgroup.  With those, a 64 x 64 step took 15 us of
+// GPU time, 3 us of it in the chain of atomics at its end.
+__device__ inline void finish_closed(const CflSlots &c, const InstRow *inst, const double *dt_in,
+                                     double dt_override, double cfl_desired) {
+  double lvl = 0.0;
+  for (int k = (int)threadIdx.x; k < c.n_inst; k += kThreads) {
+    const InstMin m = c.inst_min[k];
+    const double cs = inst[k].c;
+    double dt = dt_override > 0.0 ? dt_override : dt_in[k];
+    const double cfl = fmax(cs * (dt / m.dx), cs * (dt / m.dy));
+    c.cfl_last[k] = cfl;
+    c.cfl_max[k] = fmax(c.cfl_max[k], cfl);
+    if (cfl_desired > 0.0 && cfl > 0.0) dt = dt * cfl_desired / cfl;
+    c.dt[k] = dt;
+    lvl = fmax(lvl, cfl);
+  }
+  file_level(lvl, c.level_last);
+}
+
+// Heterogeneous medium: a workgroup's running maximum over consecutive tiles
+// of one instance, filed into its XCD group's slot with one atomic max per run.  The atomic returns
 // and is waited for before the workgroup retires.
 struct CflRun {
   int inst = -1;
@@ -1486,10 +1483,12 @@ __device__ inline void flush_cfl(const StepArgs &a, int group, CflRun &run) {
 }
 
 // Thread 0 after a tile: record the tile's value (for the per-patch array)
-// where every XCD can read it, and fold it into the running maximum.
+// and, in a medium, fold it into the running maximum.
+template <bool VAR>
 __device__ inline void file_tile(const StepArgs &a, int group, CflRun &run, int t, double m,
                                  int inst) {
   __hip_atomic_store(&a.slots.cfl_tile[t], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if constexpr (!VAR) return;
   if (inst != run.inst) {
     flush_cfl(a, group, run);
     run.inst = inst;
@@ -1527,13 +1526,20 @@ __device__ __attribute__((always_inline)) inline void step_body(const StepArgs &
       double m = do_unit<T, LIM, MASKS, VARS, TC, VAR>(a, t, wave, inst);
       if constexpr (VAR) m = tile_max(m, lane, wave);
       if (lane == 0 && wave == 0) {
-        file_tile(a, 0, run, t, m, inst);
-        flush_cfl(a, 0, run);
+        file_tile<VAR>(a, 0, run, t, m, inst);
+        if constexpr (VAR) flush_cfl(a, 0, run);
       }
     }
     return;
   }
-  const int G = (int)gridDim.x;
+  // homogeneous levels: one workgroup past the tiles' files the step
+  const int G = (int)gridDim.x - (VAR ? 0 : 1);
+  if constexpr (!VAR) {
+    if ((int)blockIdx.x == G) {
+      finish_closed(a.slots, a.inst, a.dt, a.dt_override, a.cfl_desired);
+      return;
+    }
+  }
   const int groups = min(kGroups, G);
   const int x = (int)blockIdx.x % groups, y = (int)blockIdx.x / groups;
   const int in_group = G / groups + (x < G % groups ? 1 : 0);
@@ -1543,8 +1549,9 @@ __device__ __attribute__((always_inline)) inline void step_body(const StepArgs &
     int inst = 0;
     double m = do_unit<T, LIM, MASKS, VARS, TC, VAR>(a, t, wave, inst);
     if constexpr (VAR) m = tile_max(m, lane, wave);
-    if (lane == 0 && wave == 0) file_tile(a, x, run, t, m, inst);
+    if (lane == 0 && wave == 0) file_tile<VAR>(a, x, run, t, m, inst);
   }
+  if constexpr (!VAR) return;
   // Retire: the workgroup's values are filed (and waited for) before its
   // count; the last workgroup of each run counts the run, and the last run's
   // last workgroup files the step and rewinds the counters for the next launch.
@@ -1564,7 +1571,7 @@ __device__ __attribute__((always_inline)) inline void step_body(const StepArgs &
   }
   __syncthreads();
   if (s_last) {
-    finish_step(a.slots, a.dt_override, a.cfl_desired);
+    finish_step(a.slots, a.dt, a.dt_override, a.cfl_desired);
     if (threadIdx.x <= kGroups)
       __hip_atomic_store(&a.retire[threadIdx.x * kLine], 0u, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
@@ -1645,12 +1652,11 @@ __global__ __launch_bounds__(kThreads) void link_ghosts_kernel(const PatchRow *p
 // --------------------------------------------------------------------------
 // dt and Courant-number bookkeeping
 // --------------------------------------------------------------------------
-__global__ void set_dt_kernel(double *dt, int n, double value) {
-  for (int k = threadIdx.x; k < n; k += blockDim.x) dt[k] = value;
-}
-
-__global__ __launch_bounds__(kThreads) void finish_step_kernel(CflSlots c, double cfl_desired) {
-  finish_step(c, 0.0, cfl_desired);
+__global__ __launch_bounds__(kThreads) void finish_step_kernel(StepArgs a) {
+  if (a.medium)
+    finish_step(a.slots, a.dt, a.dt_override, a.cfl_desired);
+  else
+    finish_closed(a.slots, a.inst, a.dt, a.dt_override, a.cfl_desired);
 }
 
 // Per-patch Courant numbers of the last step (the per-patch maximum-speed array
@@ -1802,32 +1808,6 @@ hipError_t launch_step_var_l(int vars, const StepArgs &a, int grid, hipStream_t 
   return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_step_var(int lim, int vars, const StepArgs &a, int grid, hipStream_t s) {
-  if (a.masks) return hipErrorInvalidValue;
-  switch (lim) {
-    case WS_LIM_NONE: return launch_step_var_l<T, WS_LIM_NONE>(vars, a, grid, s);
-    case WS_LIM_VANLEER: return launch_step_var_l<T, WS_LIM_VANLEER>(vars, a, grid, s);
-    default: return launch_step_var_l<T, WS_LIM_MC>(vars, a, grid, s);
-  }
-}
-
-// limiter: WS_LIM_*, optionally with WS_TRANSVERSE_CORR or kMediumFlag.
-template <typename T>
-hipError_t launch_step_l(int limiter, int vars, const StepArgs &a, int grid, hipStream_t s) {
-  if (limiter & kMediumFlag) {
-    if (vars < 1 || vars > 3 || !a.medium || (limiter & WS_TRANSVERSE_CORR))
-      return hipErrorInvalidValue;
-    return launch_step_var<T>(limiter & 0xff, vars, a, grid, s);
-  }
-  const bool tc = (limiter & WS_TRANSVERSE_CORR) != 0;
-  switch (limiter & ~WS_TRANSVERSE_CORR) {
-    case WS_LIM_NONE: return launch_step_m<T, WS_LIM_NONE>(tc, vars, a, grid, s);
-    case WS_LIM_VANLEER: return launch_step_m<T, WS_LIM_VANLEER>(tc, vars, a, grid, s);
-    default: return launch_step_m<T, WS_LIM_MC>(tc, vars, a, grid, s);
-  }
-}
-
 template <typename T, int LIM, bool TC>
 int occupancy_of(int vars, int *n) {
   hipError_t e;
@@ -1861,20 +1841,6 @@ int occupancy_of(int vars, int *n) {
 }
 
 template <typename T, int LIM>
-int occupancy_t(bool tc, int vars, int *n) {
-  return tc ? occupancy_of<T, LIM, true>(vars, n) : occupancy_of<T, LIM, false>(vars, n);
-}
-
-}  // namespace
-
-hipError_t launch_step(int dtype, int limiter, int vars, const StepArgs &a, int grid,
-                       hipStream_t s) {
-  if (grid <= 0) return hipSuccess;
-  return dtype == WS_F32 ? launch_step_l<float>(limiter, vars, a, grid, s)
-                         : launch_step_l<double>(limiter, vars, a, grid, s);
-}
-
-template <typename T, int LIM>
 int occupancy_var(int vars, int *n) {
   hipError_t e;
   if (vars == 2)
@@ -1886,21 +1852,88 @@ int occupancy_var(int vars, int *n) {
   return e == hipSuccess ? 0 : -1;
 }
 
-template <typename T>
-int occupancy_l(int limiter, int vars, int *wg_per_cu) {
+}  // namespace
+
+// The step kernels of one type and limiter.  limiter: WS_LIM_*, optionally
+// with WS_TRANSVERSE_CORR or kMediumFlag.  The build compiles this file once
+// per instance (WS_PART 1 .. 6) and once for the rest (WS_PART 0), so that
+// the instances compile in parallel; without WS_PART it holds everything.
+template <typename T, int LIM>
+hipError_t launch_step_of(int limiter, int vars, const StepArgs &a, int grid, hipStream_t s) {
   if (limiter & kMediumFlag) {
-    switch (limiter & 0xff) {
-      case WS_LIM_NONE: return occupancy_var<T, WS_LIM_NONE>(vars, wg_per_cu);
-      case WS_LIM_VANLEER: return occupancy_var<T, WS_LIM_VANLEER>(vars, wg_per_cu);
-      default: return occupancy_var<T, WS_LIM_MC>(vars, wg_per_cu);
-    }
+    if (vars < 1 || vars > 3 || !a.medium || a.masks || (limiter & WS_TRANSVERSE_CORR))
+      return hipErrorInvalidValue;
+    return launch_step_var_l<T, LIM>(vars, a, grid, s);
   }
-  const bool tc = (limiter & WS_TRANSVERSE_CORR) != 0;
-  switch (limiter & ~WS_TRANSVERSE_CORR) {
-    case WS_LIM_NONE: return occupancy_t<T, WS_LIM_NONE>(tc, vars, wg_per_cu);
-    case WS_LIM_VANLEER: return occupancy_t<T, WS_LIM_VANLEER>(tc, vars, wg_per_cu);
-    default: return occupancy_t<T, WS_LIM_MC>(tc, vars, wg_per_cu);
+  return launch_step_m<T, LIM>((limiter & WS_TRANSVERSE_CORR) != 0, vars, a, grid, s);
+}
+
+template <typename T, int LIM>
+int step_occupancy_of(int limiter, int vars, int *n) {
+  if (limiter & kMediumFlag) return occupancy_var<T, LIM>(vars, n);
+  return (limiter & WS_TRANSVERSE_CORR) ? occupancy_of<T, LIM, true>(vars, n)
+                                        : occupancy_of<T, LIM, false>(vars, n);
+}
+
+#ifdef WS_PART
+#if WS_PART == 0
+#define WS_INSTANCE(T, LIM)                                                             \
+  extern template hipError_t launch_step_of<T, LIM>(int, int, const StepArgs &, int, hipStream_t); \
+  extern template int step_occupancy_of<T, LIM>(int, int, int *);
+WS_INSTANCE(double, WS_LIM_MC)
+WS_INSTANCE(double, WS_LIM_NONE)
+WS_INSTANCE(double, WS_LIM_VANLEER)
+WS_INSTANCE(float, WS_LIM_MC)
+WS_INSTANCE(float, WS_LIM_NONE)
+WS_INSTANCE(float, WS_LIM_VANLEER)
+#else
+#define WS_INSTANCE(T, LIM)                                                                  \
+  template hipError_t launch_step_of<T, LIM>(int, int, const StepArgs &, int, hipStream_t);  \
+  template int step_occupancy_of<T, LIM>(int, int, int *);
+#if WS_PART == 1
+WS_INSTANCE(double, WS_LIM_MC)
+#elif WS_PART == 2
+WS_INSTANCE(double, WS_LIM_NONE)
+#elif WS_PART == 3
+WS_INSTANCE(double, WS_LIM_VANLEER)
+#elif WS_PART == 4
+WS_INSTANCE(float, WS_LIM_MC)
+#elif WS_PART == 5
+WS_INSTANCE(float, WS_LIM_NONE)
+#else
+WS_INSTANCE(float, WS_LIM_VANLEER)
+#endif
+#endif
+#endif
+
+#if !defined(WS_PART) || WS_PART == 0
+template <typename T>
+static hipError_t launch_step_l(int limiter, int vars, const StepArgs &a, int grid,
+                                hipStream_t s) {
+  switch (limiter & 0xff) {
+    case WS_LIM_NONE: return launch_step_of<T, WS_LIM_NONE>(limiter, vars, a, grid, s);
+    case WS_LIM_VANLEER: return launch_step_of<T, WS_LIM_VANLEER>(limiter, vars, a, grid, s);
+    default: return launch_step_of<T, WS_LIM_MC>(limiter, vars, a, grid, s);
   }
+}
+
+template <typename T>
+static int occupancy_l(int limiter, int vars, int *wg_per_cu) {
+  switch (limiter & 0xff) {
+    case WS_LIM_NONE: return step_occupancy_of<T, WS_LIM_NONE>(limiter, vars, wg_per_cu);
+    case WS_LIM_VANLEER: return step_occupancy_of<T, WS_LIM_VANLEER>(limiter, vars, wg_per_cu);
+    default: return step_occupancy_of<T, WS_LIM_MC>(limiter, vars, wg_per_cu);
+  }
+}
+
+hipError_t launch_step(int dtype, int limiter, int vars, const StepArgs &a, int grid,
+                       hipStream_t s) {
+  if (grid <= 0) return hipSuccess;
+  // a homogeneous level's persistent launch has one more workgroup, which
+  // files the Courant numbers
+  if (a.persistent && !(limiter & kMediumFlag)) ++grid;
+  return dtype == WS_F32 ? launch_step_l<float>(limiter, vars, a, grid, s)
+                         : launch_step_l<double>(limiter, vars, a, grid, s);
 }
 
 int step_occupancy(int dtype, int limiter, int vars, int *wg_per_cu) {
@@ -1936,13 +1969,8 @@ hipError_t launch_link_ghosts(int dtype, const PatchRow *patches, int n_patches,
   return hipGetLastError();
 }
 
-hipError_t launch_set_dt(const CflSlots &c, double value, hipStream_t s) {
-  hipLaunchKernelGGL(set_dt_kernel, dim3(1), dim3(256), 0, s, c.dt, c.n_inst, value);
-  return hipGetLastError();
-}
-
-hipError_t launch_finish_step(const CflSlots &c, double cfl_desired, hipStream_t s) {
-  hipLaunchKernelGGL(finish_step_kernel, dim3(1), dim3(kThreads), 0, s, c, cfl_desired);
+hipError_t launch_finish_step(const StepArgs &a, hipStream_t s) {
+  hipLaunchKernelGGL(finish_step_kernel, dim3(1), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1971,5 +1999,7 @@ hipError_t launch_sums(int dtype, const PatchRow *patches, int n_patches, const 
                      patch_sums, sums);
   return hipGetLastError();
 }
+
+#endif  // WS_PART
 
 }  // namespace ws
