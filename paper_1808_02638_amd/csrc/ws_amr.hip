@@ -78,11 +78,11 @@ __device__ inline void xedge_terms(const Q &q, const Coef<T> &k, int e, int j, T
                 s1(Z, q.P(e - 1, j + 1) - q.P(e - 1, j), q.V(e - 1, j + 1) - q.V(e - 1, j));
   const T ysr = s2(Z, q.P(e, j) - q.P(e, j - 1), q.V(e, j) - q.V(e, j - 1)) +
                 s1(Z, q.P(e, j + 1) - q.P(e, j), q.V(e, j + 1) - q.V(e, j));
-  T Fp, Fu;
-  ftilde<T, LIM>(k, a1, a2, a1r, a2l, ysl, ysr, Fp, Fu);
+  T c1, c2;
+  ftilde<T, LIM>(k, a1, a2, a1r, a2l, ysl, ysr, c1, c2);
   am[0] = k.h * a1, am[1] = -(k.hz * a1), am[2] = T(0);
   ap[0] = k.h * a2, ap[1] = k.hz * a2, ap[2] = T(0);
-  F[0] = Fp, F[1] = Fu, F[2] = T(0);
+  F[0] = c2 - c1, F[1] = (c1 + c2) * k.iz, F[2] = T(0);
 }
 
 // Terms at y-edge (i, f - 1/2): B-dQ, B+dQ, G~.
@@ -98,11 +98,11 @@ __device__ inline void yedge_terms(const Q &q, const Coef<T> &k, int i, int f, T
                 s1(Z, q.P(i + 1, f - 1) - q.P(i, f - 1), q.U(i + 1, f - 1) - q.U(i, f - 1));
   const T xsh = s2(Z, q.P(i, f) - q.P(i - 1, f), q.U(i, f) - q.U(i - 1, f)) +
                 s1(Z, q.P(i + 1, f) - q.P(i, f), q.U(i + 1, f) - q.U(i, f));
-  T Gp, Gv;
-  gtilde<T, LIM>(k, b1, b2, b1u, b2d, xsl, xsh, Gp, Gv);
+  T c1, c2;
+  gtilde<T, LIM>(k, b1, b2, b1u, b2d, xsl, xsh, c1, c2);
   bm[0] = k.h * b1, bm[1] = T(0), bm[2] = -(k.hz * b1);
   bp[0] = k.h * b2, bp[1] = T(0), bp[2] = k.hz * b2;
-  G[0] = Gp, G[1] = T(0), G[2] = Gv;
+  G[0] = c2 - c1, G[1] = T(0), G[2] = (c1 + c2) * k.iz;
 }
 
 // Side of a fine patch an edge index falls on: edges are numbered left
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(kThreads) void cf_fine_step_kernel(CfArgs a, int st
   if (b >= 2 * nxb + 2 * nyb) {
     // coarse interface edges, from the coarse state before its step
     const InstRow ic = a.cinst[cp.inst];
-    const Coef<T> kc = make_coef<T>(ic.c, ic.Z, dt, cp.dx, cp.dy);
+    const Coef<T> kc = make_coef<T, LIM>(ic.c, ic.Z, dt, cp.dx, cp.dy);
     const int e = (b - 2 * nxb - 2 * nyb) * S + t;
     if (e < 2 * (pl.ncx + pl.ncy)) coarse_edge<T, LIM>(a, pl, co, kc, e);
     return;
@@ -446,7 +446,7 @@ __global__ __launch_bounds__(kThreads) void cf_fine_step_kernel(CfArgs a, int st
   // this fine step's slots of the patch's boundary edges
   double *acc = a.acc + 3 * ((int64_t)step * a.n_fedges + pl.fedge0);
   const InstRow in = a.finst[fp.inst];
-  const Coef<T> k = make_coef<T>(in.c, in.Z, dt_fine, fp.dx, fp.dy);
+  const Coef<T> k = make_coef<T, LIM>(in.c, in.Z, dt_fine, fp.dx, fp.dy);
   const View<T> q = view<T>(a.f_cur, fp);
   const FineGhost<T> G = fine_ghost<T>(a, pl, cp, (double)step / r);
   if (b < 2 * nxb) {

@@ -349,9 +349,20 @@ struct ws_ctx {
       for (const PatchRow &r : rows) n += ceil_div(r.mx, kMultiCols) * ceil_div(r.my, 4 * seg);
       return n;
     };
-    two_rows = 4;
-    while (two_rows < kMaxMarchRows && count(two_rows) > 2 * (int64_t)n_cu) ++two_rows;
-    if (const char *e = getenv("WS_TWO_ROWS")) two_rows = atoi(e);
+    // Rows per segment, 4 to kMaxTwoRows: a segment costs its rows plus about
+    // seven (the first step's four extra rows and the start of the march);
+    // the level costs one segment's time while every workgroup is resident at
+    // once (less when they share their CU with fewer others), and a segment's
+    // time per round of them plus half of one for the last round after that.
+    // Measured (FP64, us per step): 2048^2 at 26 rows, 740 workgroups on 768
+    // places, 20.9; at 20 rows, 962 of them, 22.0; 13 rows 21.7, 8 rows 22.8.
+    const double places = (double)n_cu * std::max(1, step_two_occupancy(dtype, limiter));
+    double best = 0.0;
+    for (int seg = 4; seg <= kMaxTwoRows; ++seg) {
+      const double rounds = count(seg) / places;
+      const double cost = (seg + 7) * (rounds <= 1.0 ? 0.6 + 0.4 * rounds : rounds + 0.5);
+      if (seg == 4 || cost < best) best = cost, two_rows = seg;
+    }
     if ((int64_t)tiles.size() + count(two_rows) > L.max_tiles) return;
     for (int k : order) {
       const PatchRow &r = rows[k];

@@ -19,8 +19,16 @@ struct Coef {
   T fx, fxz, fy, fyz;     // c(1-nu)/4 and /Z: correction factors
   T gx, gxz, gy, gyz;     // dtdx c^2/8 and /Z: transverse factors
   T dtdx, dtdy;
-  T tx, ty;               // 1 - nu: the correction moved into the split vectors
+  T iz, dtdxz, dtdyz;     // 1/Z, dtdx/Z, dtdy/Z
+  T lx, ly;               // fx, fy on the limiter's scale
+  T tx, ty;               // 1 - nu on it: the correction moved into the split vectors
 };
+
+// limited() returns its strength divided by this power of two (it goes into
+// the factors, exactly).
+constexpr double limiter_scale(int lim) {
+  return lim == WS_LIM_NONE ? 1.0 : lim == WS_LIM_VANLEER ? 2.0 : 0.5;
+}
 
 // Wave-uniform values are moved to scalar registers.
 __device__ inline double uniform(double v) {
@@ -31,7 +39,7 @@ __device__ inline float uniform(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
-template <typename T>
+template <typename T, int LIM = WS_LIM_NONE>
 __device__ inline Coef<T> make_coef(double c, double Z, double dt, double dx, double dy) {
   const double dtdx = dt / dx, dtdy = dt / dy, iz = 1.0 / Z;
   const double fx = 0.25 * c * (1.0 - c * dtdx), fy = 0.25 * c * (1.0 - c * dtdy);
@@ -50,8 +58,13 @@ __device__ inline Coef<T> make_coef(double c, double Z, double dt, double dx, do
   k.gyz = (T)(gy * iz);
   k.dtdx = (T)dtdx;
   k.dtdy = (T)dtdy;
-  k.tx = (T)(1.0 - c * dtdx);
-  k.ty = (T)(1.0 - c * dtdy);
+  k.iz = (T)iz;
+  k.dtdxz = (T)(dtdx * iz);
+  k.dtdyz = (T)(dtdy * iz);
+  k.lx = (T)(limiter_scale(LIM) * fx);
+  k.ly = (T)(limiter_scale(LIM) * fy);
+  k.tx = (T)(limiter_scale(LIM) * (1.0 - c * dtdx));
+  k.ty = (T)(limiter_scale(LIM) * (1.0 - c * dtdy));
   T *f = &k.Z;
   for (int n = 0; n < (int)(sizeof(Coef<T>) / sizeof(T)); ++n) f[n] = uniform(f[n]);
   return k;
@@ -87,9 +100,34 @@ __device__ inline float shl(float v) { return __int_as_float(dpp_shl_i(__float_a
 
 // --------------------------------------------------------------------------
 // Limiter on unscaled strengths: psi(a, a_up) = phi(a_up/a) a (the limiters
-// are positively homogeneous).  MC: minmod(2a, 2a_up, (a + a_up)/2), written
-// branch-free.
+// are positively homogeneous), divided by limiter_scale(LIM).  MC:
+// minmod(2a, 2a_up, (a + a_up)/2).  FP64: min(4 min(a, a_up), a + a_up), half
+// of it, on |a| and on a_up with a's sign taken out of it (a negative minimum:
+// the signs differ, and the result is 0); five FP64 and three integer
+// instructions, where max(min(2a, 2a_up, m), 0) + min(max(2a, 2a_up, m), 0)
+// takes eleven.  The minima are written as instructions because the compiler
+// first quiets every operand whose bits were edited (two more each).  FP32:
+// the median of (0, x, y) is minmod(x, y), so four instructions instead of
+// nine.
 // --------------------------------------------------------------------------
+__device__ inline double flip(double v, int sign) {
+  return __hiloint2double(__double2hiint(v) ^ sign, __double2loint(v));
+}
+__device__ inline double min_abs(double a, double b) {  // min(|a|, b)
+  double r;
+  asm("v_min_f64 %0, |%1|, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ inline double min_raw(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ inline double max_zero(double a) {
+  double r;
+  asm("v_max_f64 %0, %1, 0" : "=v"(r) : "v"(a));
+  return r;
+}
 template <typename T, int LIM>
 __device__ inline T limited(T a, T b) {
   if constexpr (LIM == WS_LIM_NONE) {
@@ -97,13 +135,16 @@ __device__ inline T limited(T a, T b) {
   } else if constexpr (LIM == WS_LIM_VANLEER) {
     // van Leer, phi(theta) = (theta + |theta|)/(1 + |theta|) with theta = b/a:
     // 0 unless a and b share a sign, then 2ab/(a + b)
-    const T ab = a * b;
-    return ab > T(0) ? (ab + ab) / (a + b) : T(0);
+    // (the quotient is formed either way: a select costs less than a branch)
+    const T ab = a * b, r = ab / (a + b);
+    return ab > T(0) ? r : T(0);
+  } else if constexpr (sizeof(T) == 4) {
+    const float t = __builtin_amdgcn_fmed3f(0.0f, a, b);
+    return __builtin_amdgcn_fmed3f(0.0f, a + b, 4.0f * t);
   } else {
-    const T ta = a + a, tb = b + b, m = (a + b) * T(0.5);
-    const T lo = fmin(fmin(ta, tb), m);
-    const T hi = fmax(fmax(ta, tb), m);
-    return fmax(lo, T(0)) + fmin(hi, T(0));
+    const int sign = __double2hiint(a) & (int)0x80000000;
+    const double y = flip(b, sign);
+    return flip(max_zero(min_raw(4.0 * min_abs(a, y), fabs(a) + y)), sign);
   }
 }
 
@@ -113,50 +154,57 @@ __device__ inline T s1(T Z, T dp, T dn) { return fma(Z, dn, -dp); }
 template <typename T>
 __device__ inline T s2(T Z, T dp, T dn) { return fma(Z, dn, dp); }
 
-// F~ at an x-edge from the limited strengths of its two waves (l1 of wave -c,
-// l2 of wave +c): the normal correction plus the transverse waves A-+ split
-// from the y-terms of the cells left and right.
+// F~ at an x-edge is carried in characteristic form: with the limited
+// strengths l1, l2 of the waves -c, +c and the y-fluctuation sums of the cells
+// left and right,
+//   F~_p = c2 - c1, Z F~_u = c2 + c1, c2 = fx l2 - gy ys_left,
+//   c1 = fx l1 - gy ys_right,
+// since the transverse waves A-+ of a y-term reach one characteristic each.
+// Two multiplies and two FMAs per edge instead of ten operations.
 template <typename T>
-__device__ inline void ftilde_l(const Coef<T> &k, T l1, T l2, T ys_left, T ys_right, T &Fp,
-                                T &Fu) {
-  const T Fcp = k.fx * (l2 - l1), Fcu = k.fxz * (l1 + l2);
-  Fp = Fcp - k.gy * (ys_left - ys_right);
-  Fu = Fcu - k.gyz * (ys_right + ys_left);
+__device__ inline void ftilde_l(const Coef<T> &k, T l1, T l2, T ys_left, T ys_right, T &c1,
+                                T &c2) {
+  c1 = fma(-k.gy, ys_right, k.lx * l1);
+  c2 = fma(-k.gy, ys_left, k.lx * l2);
 }
 
-// G~ at a y-edge, the mirror image: transverse waves B-+ split from the
-// x-terms of the cells below (lo) and above (hi).
+// G~ at a y-edge, the mirror image: the x-terms of the cells below (lo) and
+// above (hi).
 template <typename T>
-__device__ inline void gtilde_l(const Coef<T> &k, T l1, T l2, T xs_lo, T xs_hi, T &Gp, T &Gv) {
-  const T Gcp = k.fy * (l2 - l1), Gcv = k.fyz * (l1 + l2);
-  Gp = Gcp - k.gx * (xs_lo - xs_hi);
-  Gv = Gcv - k.gxz * (xs_hi + xs_lo);
+__device__ inline void gtilde_l(const Coef<T> &k, T l1, T l2, T xs_lo, T xs_hi, T &c1, T &c2) {
+  c1 = fma(-k.gx, xs_hi, k.ly * l1);
+  c2 = fma(-k.gx, xs_lo, k.ly * l2);
 }
 
 // F~ from the raw strengths (wave -c takes its upwind neighbour on the right,
 // wave +c on the left) and the y-fluctuations of the cells left and right.
 template <typename T, int LIM>
 __device__ inline void ftilde(const Coef<T> &k, T a1, T a2, T a1_right, T a2_left, T ys_left,
-                              T ys_right, T &Fp, T &Fu) {
+                              T ys_right, T &c1, T &c2) {
   ftilde_l<T>(k, limited<T, LIM>(a1, a1_right), limited<T, LIM>(a2, a2_left), ys_left, ys_right,
-              Fp, Fu);
+              c1, c2);
 }
 
 // G~ from the raw strengths and the x-fluctuations of the cells below and above.
 template <typename T, int LIM>
 __device__ inline void gtilde(const Coef<T> &k, T b1, T b2, T b1_up, T b2_down, T xs_lo, T xs_hi,
-                              T &Gp, T &Gv) {
-  gtilde_l<T>(k, limited<T, LIM>(b1, b1_up), limited<T, LIM>(b2, b2_down), xs_lo, xs_hi, Gp, Gv);
+                              T &c1, T &c2) {
+  gtilde_l<T>(k, limited<T, LIM>(b1, b1_up), limited<T, LIM>(b2, b2_down), xs_lo, xs_hi, c1, c2);
 }
 
-// Flux-differencing update of one cell, eq. (2.3).
+// Flux-differencing update of one cell, eq. (2.3), from the strengths that
+// enter it (a2 of its left and a1 of its right edge, b2 of its bottom and b1
+// of its top edge) and the characteristic F~, G~ of its four edges: the
+// fluctuation h (a2 +- a1) and the flux difference meet per characteristic.
 template <typename T>
-__device__ inline void update(const Coef<T> &k, T p0, T u0, T v0, T xs0, T xd0, T ys0, T yd0,
-                              T FLp, T FLu, T FRp, T FRu, T GBp, T GBv, T GTp, T GTv, T &pn, T &un,
+__device__ inline void update(const Coef<T> &k, T p0, T u0, T v0, T a2L, T a1R, T b2B, T b1T,
+                              T FL1, T FL2, T FR1, T FR2, T GB1, T GB2, T GT1, T GT2, T &pn, T &un,
                               T &vn) {
-  pn = p0 - k.dtdx * (k.h * xs0 + (FRp - FLp)) - k.dtdy * (k.h * ys0 + (GTp - GBp));
-  un = u0 - k.dtdx * (k.hz * xd0 + (FRu - FLu));
-  vn = v0 - k.dtdy * (k.hz * yd0 + (GTv - GBv));
+  const T x2 = fma(k.h, a2L, FR2 - FL2), x1 = fma(k.h, a1R, FL1 - FR1);
+  const T y2 = fma(k.h, b2B, GT2 - GB2), y1 = fma(k.h, b1T, GB1 - GT1);
+  pn = p0 - fma(k.dtdy, y2 + y1, k.dtdx * (x2 + x1));  // one rounding at p's size
+  un = fma(-k.dtdxz, x2 - x1, u0);
+  vn = fma(-k.dtdyz, y2 - y1, v0);
 }
 
 // Raw buffer stores (gfx9 buffer resource, no format conversion).  An offset
@@ -168,13 +216,24 @@ constexpr int kRawBufferWord3 = 0x00020000;
 constexpr unsigned kDropOffset = 0x80000000u;
 constexpr int kStoreDeviceScope = 16;  // SC1
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-__device__ inline void bstore(__amdgpu_buffer_rsrc_t r, double v, unsigned off) {
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, 0,
+// off: per lane; soff: the same for the wavefront (a scalar register).  Only
+// off decides whether a lane's store is dropped.
+__device__ inline void bstore(__amdgpu_buffer_rsrc_t r, double v, unsigned off,
+                              unsigned soff = 0) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, off, soff,
                                         kStoreDeviceScope);
 }
-__device__ inline void bstore(__amdgpu_buffer_rsrc_t r, float v, unsigned off) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, 0,
+__device__ inline void bstore(__amdgpu_buffer_rsrc_t r, float v, unsigned off,
+                              unsigned soff = 0) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, off, soff,
                                         kStoreDeviceScope);
+}
+template <typename T>
+__device__ inline T bload(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned soff) {
+  if constexpr (sizeof(T) == 8)
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0));
+  else
+    return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
 }
 
 // One row of (p, u, v) of a MARCH segment's column.

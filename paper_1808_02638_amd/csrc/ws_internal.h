@@ -61,6 +61,8 @@ hipError_t launch_step(int dtype, int limiter, int vars, const StepArgs &a, int 
 // kMultiCols columns by 4 seg_rows rows, a.cfl_desired > 0 rescales dt after
 // each of the two steps.
 hipError_t launch_step_two(int dtype, int limiter, const StepArgs &a, hipStream_t s);
+// Workgroups of that launch a CU holds at once (0: unknown).
+int step_two_occupancy(int dtype, int limiter);
 // The ghost ring of an mx x my patch in one numbering, shared by the kernels
 // that walk it and the host tables indexed by it: rows -2, -1 across the
 // padded width, rows my, my+1, then columns -2, -1, mx, mx+1 of the interior

@@ -128,8 +128,7 @@ __device__ __attribute__((always_inline)) inline void cell_update(const Planes<T
   const T b1TT = s1(Z, qp2 - qp1, vp2 - vp1);
 
   // ---- first-order fluctuations entering the cell (and its neighbours)
-  const T xs0 = a2L + a1R, xd0 = a2L - a1R;
-  const T ys0 = b2B + b1T, yd0 = b2B - b1T;
+  const T xs0 = a2L + a1R, ys0 = b2B + b1T;
   const T pdm = q.P(i - 1, j - 1), pdp = q.P(i + 1, j - 1);
   const T udm = q.U(i - 1, j - 1), udp = q.U(i + 1, j - 1);
   const T xsm = s2(Z, qm1 - pdm, q.U(i, j - 1) - udm) + s1(Z, pdp - qm1, udp - q.U(i, j - 1));
@@ -142,12 +141,12 @@ __device__ __attribute__((always_inline)) inline void cell_update(const Planes<T
   const T ysr = s2(Z, pp1 - pdp, vr0 - vrm) + s1(Z, pup - pp1, vrp - vr0);
 
   // ---- F~ and G~ on the four edges, then the update
-  T FLp, FLu, FRp, FRu, GBp, GBv, GTp, GTv;
-  ftilde<T, LIM>(k, a1L, a2L, a1R, a2LL, ysl, ys0, FLp, FLu);
-  ftilde<T, LIM>(k, a1R, a2R, a1RR, a2L, ys0, ysr, FRp, FRu);
-  gtilde<T, LIM>(k, b1B, b2B, b1T, b2BB, xsm, xs0, GBp, GBv);
-  gtilde<T, LIM>(k, b1T, b2T, b1TT, b2B, xs0, xsp, GTp, GTv);
-  update<T>(k, p0, u0, v0, xs0, xd0, ys0, yd0, FLp, FLu, FRp, FRu, GBp, GBv, GTp, GTv, pn, un, vn);
+  T FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2;
+  ftilde<T, LIM>(k, a1L, a2L, a1R, a2LL, ysl, ys0, FL1, FL2);
+  ftilde<T, LIM>(k, a1R, a2R, a1RR, a2L, ys0, ysr, FR1, FR2);
+  gtilde<T, LIM>(k, b1B, b2B, b1T, b2BB, xsm, xs0, GB1, GB2);
+  gtilde<T, LIM>(k, b1T, b2T, b1TT, b2B, xs0, xsp, GT1, GT2);
+  update<T>(k, p0, u0, v0, a2L, a1R, b2B, b1T, FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2, pn, un, vn);
 
   if constexpr (MASKS) {
     mk->own = mc_branch(a1L, a1R) | (mc_branch(a2L, a2LL) << 2) | (mc_branch(b1B, b1T) << 4) |
@@ -246,20 +245,19 @@ __device__ __attribute__((always_inline)) inline void cell_update_tc(const Plane
   const T b1B = s1(Z, p0 - qm1, v0 - vm1), b2B = s2(Z, p0 - qm1, v0 - vm1);
   const T b1T = s1(Z, qp1 - p0, vp1 - v0), b2T = s2(Z, qp1 - p0, vp1 - v0);
   const T b1TT = s1(Z, qp2 - qp1, vp2 - vp1);
-  const T xs0 = a2L + a1R, xd0 = a2L - a1R;
-  const T ys0 = b2B + b1T, yd0 = b2B - b1T;
+  const T xs0 = a2L + a1R, ys0 = b2B + b1T;
   const T xt0 = moved<T>(xs0, k.tx, ldiff<T, LIM>(a1L, a2L, a1R, a2LL),
                          ldiff<T, LIM>(a1R, a2R, a1RR, a2L));
   const T yt0 = moved<T>(ys0, k.ty, ldiff<T, LIM>(b1B, b2B, b1T, b2BB),
                          ldiff<T, LIM>(b1T, b2T, b1TT, b2B));
 
   // ---- F~ and G~ on the four edges, then the update
-  T FLp, FLu, FRp, FRu, GBp, GBv, GTp, GTv;
-  ftilde<T, LIM>(k, a1L, a2L, a1R, a2LL, ytl, yt0, FLp, FLu);
-  ftilde<T, LIM>(k, a1R, a2R, a1RR, a2L, yt0, ytr, FRp, FRu);
-  gtilde<T, LIM>(k, b1B, b2B, b1T, b2BB, xtm, xt0, GBp, GBv);
-  gtilde<T, LIM>(k, b1T, b2T, b1TT, b2B, xt0, xtp, GTp, GTv);
-  update<T>(k, p0, u0, v0, xs0, xd0, ys0, yd0, FLp, FLu, FRp, FRu, GBp, GBv, GTp, GTv, pn, un, vn);
+  T FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2;
+  ftilde<T, LIM>(k, a1L, a2L, a1R, a2LL, ytl, yt0, FL1, FL2);
+  ftilde<T, LIM>(k, a1R, a2R, a1RR, a2L, yt0, ytr, FR1, FR2);
+  gtilde<T, LIM>(k, b1B, b2B, b1T, b2BB, xtm, xt0, GB1, GB2);
+  gtilde<T, LIM>(k, b1T, b2T, b1TT, b2B, xt0, xtp, GT1, GT2);
+  update<T>(k, p0, u0, v0, a2L, a1R, b2B, b1T, FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2, pn, un, vn);
 }
 
 // --------------------------------------------------------------------------
@@ -313,9 +311,10 @@ __device__ inline void var_limited(T a1, T a2, T a1u, T a2u, T Zl, T Zr, T wl, T
 }
 
 // Normal correction (p, normal velocity) at an edge.
-template <typename T>
+template <typename T, int LIM>
 __device__ inline void var_corr(T cl, T Zl, T cr, T Zr, T l1, T l2, T dtdx, T &Fp, T &Fn) {
-  const T gl = T(0.5) * cl * (T(1) - cl * dtdx), gr = T(0.5) * cr * (T(1) - cr * dtdx);
+  constexpr T half = T(0.5 * limiter_scale(LIM));
+  const T gl = half * cl * (T(1) - cl * dtdx), gr = half * cr * (T(1) - cr * dtdx);
   Fp = gr * Zr * l2 - gl * Zl * l1;
   Fn = gl * l1 + gr * l2;
 }
@@ -341,9 +340,9 @@ __device__ inline VarLine<T> var_line_edges(const T a1[4], const T a2[4], const 
   VarLine<T> L;
   T l1, l2;
   var_limited<T, LIM>(a1[1], a2[1], a1[2], a2[0], Zc[1], Zc[2], wl, w0, l1, l2);
-  var_corr(C[1], Zc[1], C[2], Zc[2], l1, l2, dtdx, L.Fl_p, L.Fl_n);
+  var_corr<T, LIM>(C[1], Zc[1], C[2], Zc[2], l1, l2, dtdx, L.Fl_p, L.Fl_n);
   var_limited<T, LIM>(a1[2], a2[2], a1[3], a2[1], Zc[2], Zc[3], w0, wr, l1, l2);
-  var_corr(C[2], Zc[2], C[3], Zc[3], l1, l2, dtdx, L.Fr_p, L.Fr_n);
+  var_corr<T, LIM>(C[2], Zc[2], C[3], Zc[3], l1, l2, dtdx, L.Fr_p, L.Fr_n);
   L.xs = a2[1] + a1[2];
   L.xd = a2[1] - a1[2];
   L.izl = iz[1], L.izr = iz[2];
@@ -622,7 +621,7 @@ struct MarchLanes {
   bool ybc;  // extrapolation sides: ghost rows are written
   bool xbc;  // the segment touches a physical x side
   int gx;    // ghost-column lane: 1, 2 -> i = -1, -2 (copy column 0); 3, 4 -> i = mx, mx+1
-  bool st;   // lane stores
+  unsigned ocolb;  // byte offset of the lane's column in a row, or kDropOffset
 
   __device__ MarchLanes(const T *qi, T *qo, const PatchRow &pr, int l_, int i_) {
     ld = (unsigned)pr.ld;
@@ -648,13 +647,17 @@ struct MarchLanes {
       if (i == mx && l <= w - 2) gx = 3;
       if (i == mx + 1 && l <= w - 1) gx = 4;
     }
-    st = out || gx != 0;
+    ocolb = out || gx != 0 ? (unsigned)(i + 2) * (unsigned)sizeof(T) : kDropOffset;
   }
   __device__ unsigned at(int r) const {
     return ((unsigned)(r + 2) * ld + (unsigned)(ic + 2)) * (unsigned)sizeof(T);
   }
-  __device__ unsigned oat(int r) const {
-    return ((unsigned)(r + 2) * ld + (unsigned)(i + 2)) * (unsigned)sizeof(T);
+  // the row is in the scalar offset, the lane's column in the vector one
+  __device__ void put(T pn, T un, T vn, int r) const {
+    const unsigned o = (unsigned)(r + 2) * ld * (unsigned)sizeof(T);
+    bstore(ob, pn, ocolb, o);
+    bstore(ob, un, ocolb, o + plb);
+    bstore(ob, vn, ocolb, o + 2 * plb);
   }
   __device__ T get(unsigned boff) const { return *reinterpret_cast<const T *>(base + boff); }
   // rows past the ghost rows are clamped to them (the values are never used)
@@ -683,18 +686,10 @@ struct MarchLanes {
       if (gx == 3) { pn = p3; un = u3; vn = v3; }
       if (gx == 4) { pn = p4; un = u4; vn = v4; }
     }
-    const unsigned so = st ? oat(r) : kDropOffset;
-    bstore(ob, pn, so);
-    bstore(ob, un, so + plb);
-    bstore(ob, vn, so + 2 * plb);
+    put(pn, un, vn, r);
     if (ybc && (r == 0 || r == my - 1)) {
       const int g0 = r == 0 ? -2 : my;
-      for (int g = g0; g <= g0 + 1; ++g) {
-        const unsigned o = st ? oat(g) : kDropOffset;
-        bstore(ob, pn, o);
-        bstore(ob, un, o + plb);
-        bstore(ob, vn, o + 2 * plb);
-      }
+      for (int g = g0; g <= g0 + 1; ++g) put(pn, un, vn, g);
     }
   }
 };
@@ -837,8 +832,8 @@ __device__ __attribute__((always_inline)) inline void march_up(const L &M, const
   T a1L = s1(Z, P0 - pl_0, U0 - ul_0), a2L = s2(Z, P0 - pl_0, U0 - ul_0);
   T a1R = shl(a1L);
   T xs0 = a2L + a1R;
-  T GBp, GBv;
-  gtilde<T, LIM>(k, b1m, b2m, b1h, b2mm, xsm, xs0, GBp, GBv);
+  T GB1, GB2;
+  gtilde<T, LIM>(k, b1m, b2m, b1h, b2mm, xsm, xs0, GB1, GB2);
   unsigned ybits = 0;
   if constexpr (MASKS) ybits = (mc_branch(b1m, b1h) << 4) | (mc_branch(b2m, b2mm) << 6);
   const int64_t mld = M.mx + 1;
@@ -853,21 +848,20 @@ __device__ __attribute__((always_inline)) inline void march_up(const L &M, const
     const T P2 = C.p, V2 = C.v;
     // y-edge r+3/2 of this column and the y-fluctuations of cell (i, r)
     const T b1hh = s1(Z, P2 - P1, V2 - V1), b2hh = s2(Z, P2 - P1, V2 - V1);
-    const T ys0 = yb2 + b1h, yd0 = yb2 - b1h;
+    const T ys0 = yb2 + b1h;
     // left x-edge of row r+1
     const T pl_1 = shr(P1), ul_1 = shr(U1);
     const T a1Ln = s1(Z, P1 - pl_1, U1 - ul_1), a2Ln = s2(Z, P1 - pl_1, U1 - ul_1);
     const T a1Rn = shl(a1Ln);
     const T xsp = a2Ln + a1Rn;
-    const T xd0 = a2L - a1R;
     const T a2LL = shr(a2L);
     const T ysl = shr(ys0);
-    T FLp, FLu, GTp, GTv;
-    ftilde<T, LIM>(k, a1L, a2L, a1R, a2LL, ysl, ys0, FLp, FLu);
-    const T FRp = shl(FLp), FRu = shl(FLu);
-    gtilde<T, LIM>(k, b1h, b2h, b1hh, yb2, xs0, xsp, GTp, GTv);
+    T FL1, FL2, GT1, GT2;
+    ftilde<T, LIM>(k, a1L, a2L, a1R, a2LL, ysl, ys0, FL1, FL2);
+    const T FR1 = shl(FL1), FR2 = shl(FL2);
+    gtilde<T, LIM>(k, b1h, b2h, b1hh, yb2, xs0, xsp, GT1, GT2);
     T pn, un, vn;
-    update<T>(k, P0, U0, V0, xs0, xd0, ys0, yd0, FLp, FLu, FRp, FRu, GBp, GBv, GTp, GTv, pn, un, vn);
+    update<T>(k, P0, U0, V0, a2L, a1R, yb2, b1h, FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2, pn, un, vn);
     M.emit(pn, un, vn, r);
     if constexpr (MASKS) {
       const unsigned xbits = mc_branch(a1L, a1R) | (mc_branch(a2L, a2LL) << 2);
@@ -885,7 +879,7 @@ __device__ __attribute__((always_inline)) inline void march_up(const L &M, const
     }
     // slide up one row
     yb2 = b2h; b1h = b1hh; b2h = b2hh;
-    GBp = GTp; GBv = GTv;
+    GB1 = GT1; GB2 = GT2;
     xs0 = xsp; a1L = a1Ln; a2L = a2Ln; a1R = a1Rn;
     __builtin_amdgcn_sched_barrier(0);
     if (refill) M.fetch(A, r + kSets);
@@ -932,8 +926,8 @@ __device__ __attribute__((always_inline)) inline void march_down(const L &M, con
   T a1L = s1(Z, P0 - pl_0, U0 - ul_0), a2L = s2(Z, P0 - pl_0, U0 - ul_0);
   T a1R = shl(a1L);
   T xs0 = a2L + a1R;
-  T GTp, GTv;  // G~ of the cell's top edge
-  gtilde<T, LIM>(k, b1a, b2a, b1aa, b2B, xs0, xsa, GTp, GTv);
+  T GT1, GT2;  // G~ of the cell's top edge
+  gtilde<T, LIM>(k, b1a, b2a, b1aa, b2B, xs0, xsa, GT1, GT2);
 
   // One row r: A, B, C hold rows r, r-1, r-2; A is refilled with row r-kSets.
   auto row = [&](Row3<T> &A, const Row3<T> &B, const Row3<T> &C, int r, bool refill) {
@@ -943,25 +937,24 @@ __device__ __attribute__((always_inline)) inline void march_down(const L &M, con
     const T Pmm = C.p, Vmm = C.v;
     // y-edge r-3/2 of this column and the y-fluctuations of cell (i, r)
     const T b1BB = s1(Z, Pm - Pmm, Vm - Vmm), b2BB = s2(Z, Pm - Pmm, Vm - Vmm);
-    const T ys0 = b2B + b1T, yd0 = b2B - b1T;
+    const T ys0 = b2B + b1T;
     // left x-edge of row r-1
     const T pl_m = shr(Pm), ul_m = shr(Um);
     const T a1Lm = s1(Z, Pm - pl_m, Um - ul_m), a2Lm = s2(Z, Pm - pl_m, Um - ul_m);
     const T a1Rm = shl(a1Lm);
     const T xsm = a2Lm + a1Rm;
-    const T xd0 = a2L - a1R;
     const T a2LL = shr(a2L);
     const T ysl = shr(ys0);
-    T FLp, FLu, GBp, GBv;
-    ftilde<T, LIM>(k, a1L, a2L, a1R, a2LL, ysl, ys0, FLp, FLu);
-    const T FRp = shl(FLp), FRu = shl(FLu);
-    gtilde<T, LIM>(k, b1B, b2B, b1T, b2BB, xsm, xs0, GBp, GBv);
+    T FL1, FL2, GB1, GB2;
+    ftilde<T, LIM>(k, a1L, a2L, a1R, a2LL, ysl, ys0, FL1, FL2);
+    const T FR1 = shl(FL1), FR2 = shl(FL2);
+    gtilde<T, LIM>(k, b1B, b2B, b1T, b2BB, xsm, xs0, GB1, GB2);
     T pn, un, vn;
-    update<T>(k, P0, U0, V0, xs0, xd0, ys0, yd0, FLp, FLu, FRp, FRu, GBp, GBv, GTp, GTv, pn, un, vn);
+    update<T>(k, P0, U0, V0, a2L, a1R, b2B, b1T, FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2, pn, un, vn);
     M.emit(pn, un, vn, r);
     // slide down one row
     b1T = b1B; b1B = b1BB; b2B = b2BB;
-    GTp = GBp; GTv = GBv;
+    GT1 = GB1; GT2 = GB2;
     xs0 = xsm; a1L = a1Lm; a2L = a2Lm; a1R = a1Rm;
     __builtin_amdgcn_sched_barrier(0);
     if (refill) M.fetch(A, r - kSets);
@@ -1013,8 +1006,8 @@ __device__ __attribute__((always_inline)) inline void march_up_tc(const L &M, co
   T l1 = limited<T, LIM>(a1L, a1R), l2 = limited<T, LIM>(a2L, shr(a2L));
   const T d0 = l2 - l1;
   T xt0 = moved<T>(xs0, k.tx, d0, shl(d0));
-  T GBp, GBv;
-  gtilde_l<T>(k, lb1m, lb2m, xtm, xt0, GBp, GBv);
+  T GB1, GB2;
+  gtilde_l<T>(k, lb1m, lb2m, xtm, xt0, GB1, GB2);
 
   auto row = [&](Row3<T> &A, const Row3<T> &B, const Row3<T> &C, int r, bool refill) {
     __builtin_amdgcn_sched_barrier(0);
@@ -1022,7 +1015,7 @@ __device__ __attribute__((always_inline)) inline void march_up_tc(const L &M, co
     const T P1 = B.p, U1 = B.u, V1 = B.v;
     const T P2 = C.p, V2 = C.v;
     const T b1hh = s1(Z, P2 - P1, V2 - V1), b2hh = s2(Z, P2 - P1, V2 - V1);
-    const T ys0 = yb2 + b1h, yd0 = yb2 - b1h;
+    const T ys0 = yb2 + b1h;
     // top edge r+1/2: limited strengths, then the split vector's ys
     const T lb1 = limited<T, LIM>(b1h, b1hh), lb2 = limited<T, LIM>(b2h, yb2);
     const T eT = lb2 - lb1;
@@ -1034,17 +1027,16 @@ __device__ __attribute__((always_inline)) inline void march_up_tc(const L &M, co
     const T l1n = limited<T, LIM>(a1Ln, a1Rn), l2n = limited<T, LIM>(a2Ln, shr(a2Ln));
     const T dn = l2n - l1n;
     const T xtp = moved<T>(a2Ln + a1Rn, k.tx, dn, shl(dn));
-    const T xd0 = a2L - a1R;
     const T ytl = shr(yt0);
-    T FLp, FLu, GTp, GTv;
-    ftilde_l<T>(k, l1, l2, ytl, yt0, FLp, FLu);
-    const T FRp = shl(FLp), FRu = shl(FLu);
-    gtilde_l<T>(k, lb1, lb2, xt0, xtp, GTp, GTv);
+    T FL1, FL2, GT1, GT2;
+    ftilde_l<T>(k, l1, l2, ytl, yt0, FL1, FL2);
+    const T FR1 = shl(FL1), FR2 = shl(FL2);
+    gtilde_l<T>(k, lb1, lb2, xt0, xtp, GT1, GT2);
     T pn, un, vn;
-    update<T>(k, P0, U0, V0, xs0, xd0, ys0, yd0, FLp, FLu, FRp, FRu, GBp, GBv, GTp, GTv, pn, un, vn);
+    update<T>(k, P0, U0, V0, a2L, a1R, yb2, b1h, FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2, pn, un, vn);
     M.emit(pn, un, vn, r);
     yb2 = b2h; b1h = b1hh; b2h = b2hh; eB = eT;
-    GBp = GTp; GBv = GTv;
+    GB1 = GT1; GB2 = GT2;
     xs0 = a2Ln + a1Rn; xt0 = xtp; a2L = a2Ln; a1R = a1Rn; l1 = l1n; l2 = l2n;
     __builtin_amdgcn_sched_barrier(0);
     if (refill) M.fetch(A, r + kSets);
@@ -1094,8 +1086,8 @@ __device__ __attribute__((always_inline)) inline void march_down_tc(const L &M, 
   T l1 = limited<T, LIM>(a1L, a1R), l2 = limited<T, LIM>(a2L, shr(a2L));
   const T d0 = l2 - l1;
   T xt0 = moved<T>(xs0, k.tx, d0, shl(d0));
-  T GTp, GTv;
-  gtilde_l<T>(k, lb1a, lb2a, xt0, xta, GTp, GTv);
+  T GT1, GT2;
+  gtilde_l<T>(k, lb1a, lb2a, xt0, xta, GT1, GT2);
 
   auto row = [&](Row3<T> &A, const Row3<T> &B, const Row3<T> &C, int r, bool refill) {
     __builtin_amdgcn_sched_barrier(0);
@@ -1103,7 +1095,7 @@ __device__ __attribute__((always_inline)) inline void march_down_tc(const L &M, 
     const T Pm = B.p, Um = B.u, Vm = B.v;
     const T Pmm = C.p, Vmm = C.v;
     const T b1BB = s1(Z, Pm - Pmm, Vm - Vmm), b2BB = s2(Z, Pm - Pmm, Vm - Vmm);
-    const T ys0 = b2B + b1T, yd0 = b2B - b1T;
+    const T ys0 = b2B + b1T;
     // bottom edge r-1/2: limited strengths, then the split vector's ys
     const T lb1 = limited<T, LIM>(b1B, b1T), lb2 = limited<T, LIM>(b2B, b2BB);
     const T eB = lb2 - lb1;
@@ -1115,17 +1107,16 @@ __device__ __attribute__((always_inline)) inline void march_down_tc(const L &M, 
     const T l1m = limited<T, LIM>(a1Lm, a1Rm), l2m = limited<T, LIM>(a2Lm, shr(a2Lm));
     const T dm = l2m - l1m;
     const T xtm = moved<T>(a2Lm + a1Rm, k.tx, dm, shl(dm));
-    const T xd0 = a2L - a1R;
     const T ytl = shr(yt0);
-    T FLp, FLu, GBp, GBv;
-    ftilde_l<T>(k, l1, l2, ytl, yt0, FLp, FLu);
-    const T FRp = shl(FLp), FRu = shl(FLu);
-    gtilde_l<T>(k, lb1, lb2, xtm, xt0, GBp, GBv);
+    T FL1, FL2, GB1, GB2;
+    ftilde_l<T>(k, l1, l2, ytl, yt0, FL1, FL2);
+    const T FR1 = shl(FL1), FR2 = shl(FL2);
+    gtilde_l<T>(k, lb1, lb2, xtm, xt0, GB1, GB2);
     T pn, un, vn;
-    update<T>(k, P0, U0, V0, xs0, xd0, ys0, yd0, FLp, FLu, FRp, FRu, GBp, GBv, GTp, GTv, pn, un, vn);
+    update<T>(k, P0, U0, V0, a2L, a1R, b2B, b1T, FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2, pn, un, vn);
     M.emit(pn, un, vn, r);
     b1T = b1B; b1B = b1BB; b2B = b2BB; eT = eB;
-    GTp = GBp; GTv = GBv;
+    GT1 = GB1; GT2 = GB2;
     xs0 = a2Lm + a1Rm; xt0 = xtm; a2L = a2Lm; a1R = a1Rm; l1 = l1m; l2 = l2m;
     __builtin_amdgcn_sched_barrier(0);
     if (refill) M.fetch(A, r - kSets);
@@ -1174,7 +1165,7 @@ __device__ __attribute__((always_inline)) inline VarXEdge<T> var_xedge(const Row
   var_strengths(Zl, E.u, Q.p - pl, Q.u - ul, X.a1, X.a2, X.iz);
   T l1, l2;
   var_limited<T, LIM>(X.a1, X.a2, shl(X.a1), shr(X.a2), Zl, E.u, wl, E.v, l1, l2);
-  var_corr(cl, Zl, E.p, E.u, l1, l2, dtdx, X.Fp, X.Fn);
+  var_corr<T, LIM>(cl, Zl, E.p, E.u, l1, l2, dtdx, X.Fp, X.Fn);
   return X;
 }
 
@@ -1262,7 +1253,7 @@ __device__ __attribute__((always_inline)) inline double do_unit(const StepArgs &
       const InstRow in = uniform_row(a.inst[p0.inst]);
       inst = p0.inst;
       const double dt = a.dt_override > 0.0 ? a.dt_override : a.dt[p0.inst];
-      const Coef<T> k = make_coef<T>(in.c, in.Z, dt, p0.dx, p0.dy);
+      const Coef<T> k = make_coef<T, LIM>(in.c, in.Z, dt, p0.dx, p0.dy);
       if (pw.n > 0) {
         const int lx = (int)threadIdx.x & 63;
         // the lane's piece: the last whose first lane is at or before it
@@ -1305,7 +1296,7 @@ __device__ __attribute__((always_inline)) inline double do_unit(const StepArgs &
   const InstRow in = uniform_row(a.inst[pr.inst]);
   inst = pr.inst;
   const double dt = a.dt_override > 0.0 ? a.dt_override : a.dt[pr.inst];
-  const Coef<T> k = make_coef<T>(in.c, in.Z, dt, pr.dx, pr.dy);
+  const Coef<T> k = make_coef<T, LIM>(in.c, in.Z, dt, pr.dx, pr.dy);
   const int64_t org = pr.q_off + 2 * (int64_t)pr.ld + pr.col0;
   const T *qi = reinterpret_cast<const T *>(a.qin) + org;
   T *qo = reinterpret_cast<T *>(a.qout) + org;

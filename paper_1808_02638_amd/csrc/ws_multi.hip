@@ -28,8 +28,8 @@ namespace {
 template <typename T>
 struct Carry {
   T yb2, b1h, b2h;       // b2 of the cell's bottom edge; b1, b2 of its top edge
-  T GBp, GBv;            // G~ of the bottom edge
-  T xs0, a1L, a2L, a1R;  // x-fluctuation sum and x-edge strengths of the row
+  T GB1, GB2;            // G~ of the bottom edge (characteristic)
+  T a1L, a2L;            // strengths of the row's left x-edge
 };
 
 // Carry for row r from rows r-2 (p, v), r-1, r and r+1 (p, v).
@@ -51,9 +51,7 @@ __device__ __attribute__((always_inline)) inline Carry<T> carry_in(const Coef<T>
   const T pl = shr(A.p), ul = shr(A.u);
   S.a1L = s1(Z, A.p - pl, A.u - ul);
   S.a2L = s2(Z, A.p - pl, A.u - ul);
-  S.a1R = shl(S.a1L);
-  S.xs0 = S.a2L + S.a1R;
-  gtilde<T, LIM>(k, b1m, b2m, S.b1h, b2mm, xsm, S.xs0, S.GBp, S.GBv);
+  gtilde<T, LIM>(k, b1m, b2m, S.b1h, b2mm, xsm, S.a2L + shl(S.a1L), S.GB1, S.GB2);
   return S;
 }
 
@@ -66,22 +64,21 @@ __device__ __attribute__((always_inline)) inline Row3<T> row_step(const Coef<T> 
                                                                   const Row3<T> &C) {
   const T Z = k.Z;
   const T b1hh = s1(Z, C.p - B.p, C.v - B.v), b2hh = s2(Z, C.p - B.p, C.v - B.v);
-  const T ys0 = S.yb2 + S.b1h, yd0 = S.yb2 - S.b1h;
+  const T ys0 = S.yb2 + S.b1h;
   const T pl = shr(B.p), ul = shr(B.u);
   const T a1Ln = s1(Z, B.p - pl, B.u - ul), a2Ln = s2(Z, B.p - pl, B.u - ul);
-  const T a1Rn = shl(a1Ln);
-  const T xsp = a2Ln + a1Rn;
-  const T xd0 = S.a2L - S.a1R;
-  T FLp, FLu, GTp, GTv;
-  ftilde<T, LIM>(k, S.a1L, S.a2L, S.a1R, shr(S.a2L), shr(ys0), ys0, FLp, FLu);
-  const T FRp = shl(FLp), FRu = shl(FLu);
-  gtilde<T, LIM>(k, S.b1h, S.b2h, b1hh, S.yb2, S.xs0, xsp, GTp, GTv);
+  const T xsp = a2Ln + shl(a1Ln);
+  const T a1R = shl(S.a1L);
+  T FL1, FL2, GT1, GT2;
+  ftilde<T, LIM>(k, S.a1L, S.a2L, a1R, shr(S.a2L), shr(ys0), ys0, FL1, FL2);
+  const T FR1 = shl(FL1), FR2 = shl(FL2);
+  gtilde<T, LIM>(k, S.b1h, S.b2h, b1hh, S.yb2, S.a2L + a1R, xsp, GT1, GT2);
   Row3<T> N;
-  update<T>(k, A.p, A.u, A.v, S.xs0, xd0, ys0, yd0, FLp, FLu, FRp, FRu, S.GBp, S.GBv, GTp, GTv,
+  update<T>(k, A.p, A.u, A.v, S.a2L, a1R, S.yb2, S.b1h, FL1, FL2, FR1, FR2, S.GB1, S.GB2, GT1, GT2,
             N.p, N.u, N.v);
   S.yb2 = S.b2h, S.b1h = b1hh, S.b2h = b2hh;
-  S.GBp = GTp, S.GBv = GTv;
-  S.xs0 = xsp, S.a1L = a1Ln, S.a2L = a2Ln, S.a1R = a1Rn;
+  S.GB1 = GT1, S.GB2 = GT2;
+  S.a1L = a1Ln, S.a2L = a2Ln;
   return N;
 }
 
@@ -89,80 +86,95 @@ __device__ __attribute__((always_inline)) inline Row3<T> row_step(const Coef<T> 
 // as row r, then is refilled with the row kMultiSets further up.
 constexpr int kMultiSets = 6;
 
-// Lanes of one segment: lane l holds column i of the patch, lanes kHalo ..
-// 63 - kHalo are updated.  Reads take the nearest interior cell (the
-// extrapolation ghosts); 32-bit byte offsets as in a MARCH segment.
+// Lane `from` of the wavefront (a scalar) as a wave-uniform value.
+__device__ inline double lane_value(double v, int from) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), from),
+                          __builtin_amdgcn_readlane(__double2loint(v), from));
+}
+__device__ inline float lane_value(float v, int from) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), from));
+}
+
+// Lanes of one segment: lane l holds column i of the patch, lanes kMultiHalo
+// .. 63 - kMultiHalo are updated.  Reads take the nearest interior cell (the
+// extrapolation ghosts).  Rows are addressed by a scalar offset that is
+// stepped along, columns by the lane's: no vector instruction goes into
+// addresses.
 template <typename T>
 struct MultiLanes {
-  const char *base;
-  __amdgpu_buffer_rsrc_t ob;
-  unsigned ld, plb, colb, ocolb;
-  int my, rmax;
-  bool xbc;   // the wavefront holds ghost columns
-  int gx;     // ghost column: 1, 2 -> i = -1, -2; 3, 4 -> i = mx, mx+1; else 0
-  bool st;    // the lane stores
+  __amdgpu_buffer_rsrc_t ib, ob;  // the patch in the two pools, from padded cell (-2, -2)
+  unsigned ldb, plb;     // row and plane strides (bytes)
+  unsigned colb, ocolb;  // the lane's offsets in a row: the column read, the column stored
+  int my, rmax;          // rmax: last row the segment needs
+  int lo, hi;            // lanes of columns 0 and mx-1 (negative, over 63: not in the segment)
+  bool glo, ghi;         // the lane holds a ghost column of the low, the high side
 
   __device__ MultiLanes(const T *qi, T *qo, const PatchRow &pr, int i0, int l, int r1) {
     constexpr int halo = kMultiHalo;
-    ld = (unsigned)pr.ld;
+    ldb = (unsigned)pr.ld * (unsigned)sizeof(T);
     plb = (unsigned)pr.plane * (unsigned)sizeof(T);
     my = pr.my;
     rmax = min(r1 + 3, pr.my - 1);
-    base = reinterpret_cast<const char *>(qi - 2 * (int64_t)ld - 2);
-    ob = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char *>(qo - 2 * (int64_t)ld - 2), 0,
-                                           (int)(3 * plb), kRawBufferWord3);
+    const int64_t first = 2 * (int64_t)pr.ld + 2;
+    ib = __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(qi - first), 0, (int)(3 * plb),
+                                           kRawBufferWord3);
+    ob = __builtin_amdgcn_make_buffer_rsrc(qo - first, 0, (int)(3 * plb), kRawBufferWord3);
     const int i = i0 + l, mx = pr.mx;
     colb = (unsigned)(min(max(i, 0), mx - 1) + 2) * (unsigned)sizeof(T);
-    ocolb = (unsigned)(i + 2) * (unsigned)sizeof(T);
-    xbc = i0 < 0 || i0 + kMarchWidth > mx;
-    gx = i == -1 ? 1 : i == -2 ? 2 : i == mx ? 3 : i == mx + 1 ? 4 : 0;
-    const bool out = l >= halo && l < kMarchWidth - halo && i < mx;
-    // ghost columns are stored next to the updated column they copy
-    const int s = gx == 1 ? l + 1 : gx == 2 ? l + 2 : gx == 3 ? l - 1 : l - 2;
-    st = out || (gx != 0 && s >= halo && s < kMarchWidth - halo);
+    lo = -i0;
+    hi = mx - 1 - i0;
+    glo = i < 0;
+    ghi = i >= mx;
+    // ghost columns are stored by the segment that updates the column they copy
+    const int s = i < 0 ? lo : i >= mx ? hi : l;
+    const bool st = i >= -2 && i <= mx + 1 && s >= halo && s < kMarchWidth - halo;
+    ocolb = st ? (unsigned)(i + 2) * (unsigned)sizeof(T) : kDropOffset;
   }
-  __device__ void fetch(Row3<T> &S, int r) const {
-    const unsigned o = (unsigned)(min(max(r, 0), rmax) + 2) * ld * (unsigned)sizeof(T) + colb;
-    S.p = *reinterpret_cast<const T *>(base + o);
-    S.u = *reinterpret_cast<const T *>(base + o + plb);
-    S.v = *reinterpret_cast<const T *>(base + o + 2 * plb);
+  // Whether the segment holds ghost columns.
+  __device__ bool ghosts() const { return lo > 0 || hi < kMarchWidth - 1; }
+  __device__ unsigned row_offset(int r) const {
+    return (unsigned)(min(max(r, 0), rmax) + 2) * ldb;
   }
-  // The lanes on ghost columns take the new value of the nearest column.
+  __device__ void fetch_at(Row3<T> &S, unsigned o) const {
+    S.p = bload<T>(ib, colb, o);
+    S.u = bload<T>(ib, colb, o + plb);
+    S.v = bload<T>(ib, colb, o + 2 * plb);
+  }
+  __device__ void fetch(Row3<T> &S, int r) const { fetch_at(S, row_offset(r)); }
+  // The lanes on ghost columns take the new value of the nearest column
+  // (through scalar registers: two lane reads per value and side).
   __device__ void ghost_columns(Row3<T> &N) const {
-    if (!xbc) return;
-    const T p1 = shl(N.p), u1 = shl(N.u), v1 = shl(N.v);
-    const T p2 = shl(p1), u2 = shl(u1), v2 = shl(v1);
-    const T p3 = shr(N.p), u3 = shr(N.u), v3 = shr(N.v);
-    const T p4 = shr(p3), u4 = shr(u3), v4 = shr(v3);
-    if (gx == 1) N.p = p1, N.u = u1, N.v = v1;
-    if (gx == 2) N.p = p2, N.u = u2, N.v = v2;
-    if (gx == 3) N.p = p3, N.u = u3, N.v = v3;
-    if (gx == 4) N.p = p4, N.u = u4, N.v = v4;
+    if (lo > 0) {
+      const T p = lane_value(N.p, lo), u = lane_value(N.u, lo), v = lane_value(N.v, lo);
+      if (glo) N.p = p, N.u = u, N.v = v;
+    }
+    if (hi < kMarchWidth - 1) {
+      const int from = max(hi, 0);
+      const T p = lane_value(N.p, from), u = lane_value(N.u, from), v = lane_value(N.v, from);
+      if (ghi) N.p = p, N.u = u, N.v = v;
+    }
   }
-  __device__ void put(const Row3<T> &N, int r) const {
-    const unsigned o = st ? (unsigned)(r + 2) * ld * (unsigned)sizeof(T) + ocolb : kDropOffset;
-    bstore(ob, N.p, o);
-    bstore(ob, N.u, o + plb);
-    bstore(ob, N.v, o + 2 * plb);
-  }
-  __device__ void emit(Row3<T> N, int r) const {
-    ghost_columns(N);
-    put(N, r);
-    if (r == 0) put(N, -1), put(N, -2);
-    if (r == my - 1) put(N, my), put(N, my + 1);
+  __device__ void put_at(const Row3<T> &N, unsigned o) const {
+    bstore(ob, N.p, ocolb, o);
+    bstore(ob, N.u, ocolb, o + plb);
+    bstore(ob, N.v, ocolb, o + 2 * plb);
   }
 };
 
 // Rows [r0, r1) advanced by two steps.  Set j holds row r0-2+j of the input
-// at first; iteration I works the first step's row r0-2+I and, from I = 4,
-// the second step's row r0-4+I.  The first step's rows below the patch are
-// copies of its row 0 and those above it of its last row.
-template <typename T, int LIM>
+// at first; the first step's rows r0-2 .. r0+1 come before the loop, and its
+// iteration for row r works the first step's row r+2 and the second step's
+// row r.  EDGE: the segment holds ghost columns, or rows next to the patch's
+// first or last one; the first step's rows below the patch are then copies of
+// its row 0 and those above it of its last row.  The other segments' loop has
+// no branches: a wavefront alone on its SIMD issues one instruction of any
+// kind per four cycles, so what goes into branches and addresses counts.
+template <typename T, int LIM, bool EDGE>
 __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes<T> &M,
                                                                 const Coef<T> &ka,
                                                                 const Coef<T> &kb, int r0,
                                                                 int r1) {
-  const bool bottom = r0 == 0;
+  const bool bottom = EDGE && r0 == 0;
   Row3<T> R[kMultiSets], W[3], M2, M1, e0, e1;
   const int q0 = bottom ? 0 : r0 - 2;  // first row of the first step
   M.fetch(M2, q0 - 2);
@@ -175,52 +187,65 @@ __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes
   M.fetch(R[4], r0 + 2);
   M.fetch(R[5], r0 + 3);
   Carry<T> S, S2;
+  // the first step's row from sets A, B, C; A is refilled
+  auto first = [&](Row3<T> &A, const Row3<T> &B, const Row3<T> &C, int next) {
+    Row3<T> N = row_step<T, LIM>(ka, S, A, B, C);
+    if constexpr (EDGE) M.ghost_columns(N);
+    M.fetch(A, next);
+    return N;
+  };
   if (!bottom) {
     S = carry_in<T, LIM>(ka, M2, M1, R[0], R[1]);
-    e0 = row_step<T, LIM>(ka, S, R[0], R[1], R[2]);
-    M.fetch(R[0], r0 + 4);
-    e1 = row_step<T, LIM>(ka, S, R[1], R[2], R[3]);
-    M.fetch(R[1], r0 + 5);
-    M.ghost_columns(e0);
-    M.ghost_columns(e1);
+    e0 = first(R[0], R[1], R[2], r0 + 4);
+    e1 = first(R[1], R[2], R[3], r0 + 5);
   } else {
     S = carry_in<T, LIM>(ka, M2, M1, R[2], R[3]);
   }
-  W[2] = row_step<T, LIM>(ka, S, R[2], R[3], R[4]);
-  M.ghost_columns(W[2]);
-  M.fetch(R[2], r0 + 6);
-  if (bottom) e0 = W[2], e1 = W[2];
-  W[0] = row_step<T, LIM>(ka, S, R[3], R[4], R[5]);
-  M.ghost_columns(W[0]);
-  M.fetch(R[3], r0 + 7);
-  if (r0 + 1 >= M.my) W[0] = W[2];
-  S2 = carry_in<T, LIM>(kb, e0, e1, W[2], W[0]);
+  W[0] = first(R[2], R[3], R[4], r0 + 6);
+  if (bottom) e0 = W[0], e1 = W[0];
+  W[1] = first(R[3], R[4], R[5], r0 + 7);
+  if (EDGE && r0 + 1 >= M.my) W[1] = W[0];
+  S2 = carry_in<T, LIM>(kb, e0, e1, W[0], W[1]);
 
-  // one row: first step's row r+2 from sets A, B, C into Wc, then the second
-  // step's row r from Wa, Wb, Wc; set A is refilled
+  // offsets of the row stored and of the row fetched next
+  unsigned oo = (unsigned)(r0 + 2) * M.ldb, oi = M.row_offset(r0 + 8);
+  const unsigned omax = M.row_offset(M.rmax);
   auto row = [&](Row3<T> &A, const Row3<T> &B, const Row3<T> &C, const Row3<T> &Wa,
                  const Row3<T> &Wb, Row3<T> &Wc, int r) {
     __builtin_amdgcn_sched_barrier(0);
     Wc = row_step<T, LIM>(ka, S, A, B, C);
-    M.ghost_columns(Wc);
-    if (r + 2 >= M.my) Wc = Wb;
-    const Row3<T> N = row_step<T, LIM>(kb, S2, Wa, Wb, Wc);
-    M.emit(N, r);
+    if constexpr (EDGE) {
+      M.ghost_columns(Wc);
+      if (r + 2 >= M.my) {
+        asm volatile("");  // a branch taken on two rows, not selects on each
+        Wc = Wb;
+      }
+    }
     __builtin_amdgcn_sched_barrier(0);
-    M.fetch(A, r + 2 + kMultiSets);
+    Row3<T> N = row_step<T, LIM>(kb, S2, Wa, Wb, Wc);
+    if constexpr (EDGE) {
+      M.ghost_columns(N);
+      if (r == 0) M.put_at(N, 0), M.put_at(N, M.ldb);
+      if (r == M.my - 1) M.put_at(N, oo + M.ldb), M.put_at(N, oo + 2 * M.ldb);
+    }
+    M.put_at(N, oo);
+    oo += M.ldb;
+    __builtin_amdgcn_sched_barrier(0);
+    M.fetch_at(A, oi);
+    oi = min(oi + M.ldb, omax);
   };
   for (int r = r0;;) {
-    row(R[4], R[5], R[0], W[2], W[0], W[1], r);
+    row(R[4], R[5], R[0], W[0], W[1], W[2], r);
     if (++r == r1) break;
-    row(R[5], R[0], R[1], W[0], W[1], W[2], r);
+    row(R[5], R[0], R[1], W[1], W[2], W[0], r);
     if (++r == r1) break;
-    row(R[0], R[1], R[2], W[1], W[2], W[0], r);
+    row(R[0], R[1], R[2], W[2], W[0], W[1], r);
     if (++r == r1) break;
-    row(R[1], R[2], R[3], W[2], W[0], W[1], r);
+    row(R[1], R[2], R[3], W[0], W[1], W[2], r);
     if (++r == r1) break;
-    row(R[2], R[3], R[4], W[0], W[1], W[2], r);
+    row(R[2], R[3], R[4], W[1], W[2], W[0], r);
     if (++r == r1) break;
-    row(R[3], R[4], R[5], W[1], W[2], W[0], r);
+    row(R[3], R[4], R[5], W[2], W[0], W[1], r);
     if (++r == r1) break;
   }
 }
@@ -233,12 +258,27 @@ __device__ inline double next_dt(double dt, double c, const InstMin &m, double c
   return cfl > 0.0 ? dt * cfl_desired / cfl : dt;
 }
 
+// Measured on 2048 x 2048 (200 MB of state, within the Infinity Cache): FP64
+// 20.9 us per step against 40.8 with one step per launch, where 4096 x 4096
+// takes 112 against 225 and FP32 on 1999 x 1531 11.5 against 27.  What bounds
+// it now is instruction issue and memory together: 183 instructions per row
+// and wavefront for the two steps (164 of them vector), 23 us of the 47 us a
+// 2048 x 2048 launch takes, and 220 MB of traffic, 26 us.
+//
 // Workgroup t works tile t: four segments of seg_rows rows, one per
 // wavefront, stacked up the patch.  Workgroups are dispatched round-robin
 // over the XCDs; each XCD takes a contiguous run of tiles, whose halos
 // overlap.  The last workgroup files the two steps' Courant numbers.
+// Wavefronts per SIMD the registers are kept for: three (155 registers in
+// FP64 with the MC limiter; four spilled and ran 4x slower), but two for van
+// Leer in FP64, whose divisions spilled at three.
 template <typename T, int LIM>
-__global__ __launch_bounds__(kThreads, 2) void step_kernel_two(StepArgs a) {
+constexpr int two_waves() {
+  return sizeof(T) == 8 && LIM == WS_LIM_VANLEER ? 2 : 3;
+}
+
+template <typename T, int LIM>
+__global__ __launch_bounds__(kThreads, (two_waves<T, LIM>())) void step_kernel_two(StepArgs a) {
   if (blockIdx.x == gridDim.x - 1) {
     const CflSlots &c = a.slots;
     for (int k = (int)threadIdx.x; k < c.n_inst; k += kThreads) {
@@ -265,13 +305,16 @@ __global__ __launch_bounds__(kThreads, 2) void step_kernel_two(StepArgs a) {
   const double dt0 = a.dt[pr.inst];
   double cfl;
   const double dt1 = next_dt(dt0, in.c, m, a.cfl_desired, cfl);
-  const Coef<T> ka = make_coef<T>(in.c, in.Z, dt0, pr.dx, pr.dy);
-  const Coef<T> kb = make_coef<T>(in.c, in.Z, dt1, pr.dx, pr.dy);
+  const Coef<T> ka = make_coef<T, LIM>(in.c, in.Z, dt0, pr.dx, pr.dy);
+  const Coef<T> kb = make_coef<T, LIM>(in.c, in.Z, dt1, pr.dx, pr.dy);
   const int64_t org = pr.q_off + 2 * (int64_t)pr.ld + pr.col0;
   const MultiLanes<T> M(reinterpret_cast<const T *>(a.qin) + org,
                         reinterpret_cast<T *>(a.qout) + org, pr,
                         te.tx * kMultiCols - kMultiHalo, (int)threadIdx.x & 63, r1);
-  march_two<T, LIM>(M, ka, kb, r0, r1);
+  if (M.ghosts() || r0 == 0 || r1 + 2 > pr.my)
+    march_two<T, LIM, true>(M, ka, kb, r0, r1);
+  else
+    march_two<T, LIM, false>(M, ka, kb, r0, r1);
 }
 
 template <typename T>
@@ -297,6 +340,26 @@ hipError_t two_t(int limiter, const StepArgs &a, hipStream_t s) {
 hipError_t launch_step_two(int dtype, int limiter, const StepArgs &a, hipStream_t s) {
   if (a.n_tiles <= 0 || a.seg_rows <= 0) return hipErrorInvalidValue;
   return dtype == WS_F32 ? two_t<float>(limiter, a, s) : two_t<double>(limiter, a, s);
+}
+
+template <typename T, int LIM>
+static int two_occupancy_of() {
+  int n = 0;
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel_two<T, LIM>, kThreads, 0) ==
+                 hipSuccess
+             ? n
+             : 0;
+}
+
+template <typename T>
+static int two_occupancy_t(int limiter) {
+  return limiter == WS_LIM_NONE      ? two_occupancy_of<T, WS_LIM_NONE>()
+         : limiter == WS_LIM_VANLEER ? two_occupancy_of<T, WS_LIM_VANLEER>()
+                                     : two_occupancy_of<T, WS_LIM_MC>();
+}
+
+int step_two_occupancy(int dtype, int limiter) {
+  return dtype == WS_F32 ? two_occupancy_t<float>(limiter) : two_occupancy_t<double>(limiter);
 }
 
 }  // namespace ws
