@@ -149,8 +149,9 @@ int ws_set_tiling(ws_ctx *ctx, const int32_t *variant, const int32_t *tile_w,
  * rho and K per cell instead of per instance.  medium: caller-owned device
  * buffer of at least pool_bytes (it holds c, Z and 1/(Z^2 + 1) per cell,
  * laid out like the q pools), kept until ws_destroy.  Attaching switches every patch to
- * DIRECT tiles; ws_set_tiling may then choose DIRECT or MARCH tiles (not
- * PACKED), with the same results bitwise; the step then uses the
+ * the default tiles of a medium (MARCH for patches at least 60 cells wide that
+ * are not periodic, else DIRECT); ws_set_tiling may then choose DIRECT or
+ * MARCH tiles (not PACKED), with the same results bitwise; the step then uses the
  * normal solver for two media (waves along (-Z_l, 1, 0) with speed -c_l and
  * (Z_r, 1, 0) with +c_r), limits on wave vectors, splits transversely with
  * the impedances of the neighbouring cells, and reduces the Courant number
@@ -303,6 +304,31 @@ int ws_gather(ws_ctx *ctx, const void *buf, int32_t patch, int32_t comp, int32_t
               const int32_t *ij, double *out);
 int ws_add_at(ws_ctx *ctx, void *buf, int32_t patch, int32_t comp, int32_t n,
               const int32_t *ij, const double *val);
+
+/* n_steps level steps of fixed size dt with, after step s, the pressures at n
+ * cells (i_k, j_k) of a patch in traces[s*n + k] (NaN for a cell outside the
+ * interior; n = 0: none), and, with masks_dev, the branches of step s at byte
+ * s * mask_stride (as ws_step_record_masks leaves them, with its
+ * restrictions).  FP64 contexts.  The same bits as n_steps calls of
+ * ws_step_level (ws_step_record_masks), each followed by ws_gather; pairs of
+ * steps may share a launch.  last_alone != 0: the last step is a launch of its
+ * own, so the other pool holds the state before it and the Courant numbers
+ * reported are that step's.  Asynchronous on the context's stream. */
+int ws_step_traces(ws_ctx *ctx, int32_t n_steps, double dt, int32_t patch, int32_t n,
+                   const int32_t *ij, double *traces, void *masks_dev, int64_t mask_stride,
+                   int32_t last_alone);
+
+/* n_steps adjoint steps, from step n_steps - 1 down to 0: with add_first,
+ * lam_a first takes g[(n_steps - 1)*n + k] at cell (i_k, j_k) of the patch's
+ * pressure; then for each step s the adjoint step of the branches at byte
+ * s * mask_stride, and the addition of g[(s - 1)*n + k] (for s = 0 only with
+ * add_before: the row before g's first).  The buffers take turns: the result
+ * is in lam_a when n_steps is even, in lam_b when it is odd.  Each is a pool-layout
+ * buffer as for ws_adjoint_step.  Asynchronous on the context's stream. */
+int ws_adjoint_sweep(ws_ctx *ctx, int32_t n_steps, double dt, const void *masks_dev,
+                     int64_t mask_stride, int32_t patch, int32_t n, const int32_t *ij,
+                     const double *g, int32_t add_first, int32_t add_before, void *lam_a,
+                     void *lam_b);
 
 /* Timing entry (for the benchmark and the tile autotuner): enqueue n_launches
  * level steps back to back (batched persistent launch, or per_patch != 0:

@@ -26,7 +26,8 @@ EXPORTS = (
     "ws_fill_ghosts", "ws_step_level", "ws_step_level_per_patch", "ws_set_dt", "ws_step_auto",
     "ws_capture_steps", "ws_graph_launch", "ws_read_dt_cfl", "ws_read_patch_cfl",
     "ws_conservation_sums", "ws_mask_bytes", "ws_patch_layout", "ws_step_record_masks",
-    "ws_adjoint_step", "ws_gather", "ws_add_at", "ws_time_step_kernel", "ws_current_pool",
+    "ws_adjoint_step", "ws_gather", "ws_add_at", "ws_step_traces",
+    "ws_adjoint_sweep", "ws_time_step_kernel", "ws_current_pool",
     "ws_attach_medium", "ws_upload_medium", "ws_link_layout", "ws_link_level",
     "ws_cf_layout", "ws_cf_init", "ws_cf_step", "ws_cf_nest", "ws_cf_fill_fine_ghosts",
     "ws_cf_destroy", "ws_noalloc_scratch_bytes", "ws_step_level_noalloc",
@@ -96,6 +97,8 @@ def lib():
         "ws_adjoint_step": [vp, dbl, vp, vp, vp],
         "ws_gather": [vp, vp, i32, i32, i32, vp, vp],
         "ws_add_at": [vp, vp, i32, i32, i32, vp, vp],
+        "ws_step_traces": [vp, i32, dbl, i32, i32, vp, vp, vp, i64, i32],
+        "ws_adjoint_sweep": [vp, i32, dbl, vp, i64, i32, i32, vp, vp, i32, i32, vp, vp],
         "ws_time_step_kernel": [vp, i32, i32, P(dbl)],
         "ws_current_pool": [vp, P(i32)],
         "ws_attach_medium": [vp, vp, i64],

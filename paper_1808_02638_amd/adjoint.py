@@ -102,9 +102,13 @@ class AcousticsAdjoint:
         lev.upload(0, q)
         lev.fill_ghosts()
 
-    # The step loops call the C entry points directly with arguments built
-    # once (every buffer lives on the level's stream, so no stream waits are
-    # needed); the Level methods' checks have been done on the buffers here.
+    def _mask_stride(self):
+        return (self.level.mask_bytes() + 255) // 256 * 256
+
+    # The step loops are the C entry points ws_step_traces and
+    # ws_adjoint_sweep (every buffer lives on the level's stream, so no stream
+    # waits are needed); the Level methods' checks have been done on the
+    # buffers here.
     def _forward(self, p0):
         lev = self.level
         if p0.shape != (self.my, self.mx):
@@ -114,26 +118,24 @@ class AcousticsAdjoint:
         with torch.cuda.stream(lev.stream):
             traces = torch.empty((self.nsteps, self.nr), dtype=torch.float64, device=lev.device)
             self._start(p0)
-            ckpts = []
             ij, nr, dt = ctypes.c_void_p(self.ij.data_ptr()), self.nr, self.dt
             base = traces.data_ptr()
+
+            def steps(s0, s1, masks, stride):
+                C.check(L.ws_step_traces(ctx, s1 - s0, dt, 0, nr, ij,
+                                         ctypes.c_void_p(base + 8 * nr * s0), masks, stride,
+                                         int(s1 == self.nsteps)))
+
             if self.store_branches:
                 # every step records its branches; no checkpoints
-                nb = (lev.mask_bytes() + 255) // 256 * 256
-                masks = torch.empty(self.nsteps * nb, dtype=torch.uint8, device=lev.device)
-                mb = masks.data_ptr()
-                for n in range(self.nsteps):
-                    C.check(L.ws_step_record_masks(ctx, dt, ctypes.c_void_p(mb + nb * n), None))
-                    C.check(L.ws_gather(ctx, None, 0, 0, nr, ij,
-                                        ctypes.c_void_p(base + 8 * nr * n)))
-                ckpts = masks
+                nb = self._mask_stride()
+                ckpts = torch.empty(self.nsteps * nb, dtype=torch.uint8, device=lev.device)
+                steps(0, self.nsteps, ctypes.c_void_p(ckpts.data_ptr()), nb)
             else:
-                for n in range(self.nsteps):
-                    if n % self.k == 0:
-                        ckpts.append(lev.state_view(0).clone())
-                    C.check(L.ws_step_level(ctx, dt, None))
-                    C.check(L.ws_gather(ctx, None, 0, 0, nr, ij,
-                                        ctypes.c_void_p(base + 8 * nr * n)))
+                ckpts = []
+                for s0 in range(0, self.nsteps, self.k):
+                    ckpts.append(lev.state_view(0).clone())
+                    steps(s0, min(self.nsteps, s0 + self.k), None, 0)
         lev.stream.synchronize()
         return traces, ckpts
 
@@ -145,36 +147,30 @@ class AcousticsAdjoint:
             if g.shape != (self.nsteps, self.nr):
                 raise ValueError("trace cotangent has the wrong shape")
             lam, lam_next = lev.new_buffer(), lev.new_buffer()
-            if self.store_branches:
-                # the forward pass recorded every step's branches (ckpts)
-                bufs = [ctypes.c_void_p(lam.data_ptr()), ctypes.c_void_p(lam_next.data_ptr())]
-                ij, nr, dt, gb = ctypes.c_void_p(self.ij.data_ptr()), self.nr, self.dt, g.data_ptr()
-                nb, mb = (lev.mask_bytes() + 255) // 256 * 256, ckpts.data_ptr()
-                cur = 0
-                for n in range(self.nsteps - 1, -1, -1):
-                    C.check(L.ws_add_at(ctx, bufs[cur], 0, 0, nr, ij,
-                                        ctypes.c_void_p(gb + 8 * nr * n)))
-                    C.check(L.ws_adjoint_step(ctx, dt, ctypes.c_void_p(mb + nb * n), bufs[cur],
-                                              bufs[1 - cur]))
-                    cur = 1 - cur
-                grad = lev.patch_view(lam if cur == 0 else lam_next, 0)[0, 2:-2, 2:-2].clone()
-                lev.stream.synchronize()
-                return grad
-            masks = [lev.new_masks() for _ in range(min(self.k, self.nsteps))]
-            mp = [ctypes.c_void_p(m.data_ptr()) for m in masks]
             bufs = [ctypes.c_void_p(lam.data_ptr()), ctypes.c_void_p(lam_next.data_ptr())]
             ij, nr, dt, gb = ctypes.c_void_p(self.ij.data_ptr()), self.nr, self.dt, g.data_ptr()
-            cur = 0
-            for seg in range(len(ckpts) - 1, -1, -1):
-                s0, s1 = seg * self.k, min(self.nsteps, (seg + 1) * self.k)
-                lev.state_view(0).copy_(ckpts[seg])  # restore, asynchronously
-                for s in range(s0, s1):
-                    C.check(L.ws_step_record_masks(ctx, dt, mp[s - s0], None))
-                for n in range(s1 - 1, s0 - 1, -1):
-                    C.check(L.ws_add_at(ctx, bufs[cur], 0, 0, nr, ij,
-                                        ctypes.c_void_p(gb + 8 * nr * n)))
-                    C.check(L.ws_adjoint_step(ctx, dt, mp[n - s0], bufs[cur], bufs[1 - cur]))
-                    cur = 1 - cur
+            nb, cur = self._mask_stride(), 0
+
+            def sweep(s0, s1, mb):  # adjoint steps s1-1 .. s0, their branches from mb on
+                C.check(L.ws_adjoint_sweep(ctx, s1 - s0, dt, ctypes.c_void_p(mb), nb, 0, nr, ij,
+                                           ctypes.c_void_p(gb + 8 * nr * s0),
+                                           int(s1 == self.nsteps), int(s0 > 0), bufs[cur],
+                                           bufs[1 - cur]))
+                return cur ^ ((s1 - s0) & 1)
+
+            if self.store_branches:
+                # the forward pass recorded every step's branches (ckpts)
+                cur = sweep(0, self.nsteps, ckpts.data_ptr())
+            else:
+                masks = torch.empty(min(self.k, self.nsteps) * nb, dtype=torch.uint8,
+                                    device=lev.device)
+                mb = masks.data_ptr()
+                for seg in range(len(ckpts) - 1, -1, -1):
+                    s0, s1 = seg * self.k, min(self.nsteps, (seg + 1) * self.k)
+                    lev.state_view(0).copy_(ckpts[seg])  # restore, asynchronously
+                    C.check(L.ws_step_traces(ctx, s1 - s0, dt, 0, 0, None, None,
+                                             ctypes.c_void_p(mb), nb, 0))
+                    cur = sweep(s0, s1, mb)
             grad = lev.patch_view(lam if cur == 0 else lam_next, 0)[0, 2:-2, 2:-2].clone()
         lev.stream.synchronize()
         return grad

@@ -249,11 +249,13 @@ __device__ __attribute__((always_inline)) inline void adjoint_march(const AdjLan
 
 // One wavefront per workgroup: segment (tx, ty) of patch blockIdx.y, 60
 // columns by `rows` rows.  Every padded cell of lam_out is written: the
-// interior with its (folded) cotangent, the ghosts with 0.
+// interior with its (folded) cotangent, the ghosts with 0.  add: cotangents
+// added to lam_out afterwards, each by the wavefront that owns its cell (a
+// launch of its own for them took 3 us and its gap on top of the step's 9).
 __global__ __launch_bounds__(64) void adjoint_kernel(const PatchRow *patches,
                                                      const InstRow *inst, double dt,
                                                      const uint8_t *masks, const double *lam_in,
-                                                     double *lam_out, int rows) {
+                                                     double *lam_out, int rows, AdjointAdd add) {
   const PatchRow pr = uniform_row(patches[blockIdx.y]);
   const int ntx = (pr.mx + 59) / 60, nty = (pr.my + rows - 1) / rows;
   const int b = (int)blockIdx.x;
@@ -262,6 +264,10 @@ __global__ __launch_bounds__(64) void adjoint_kernel(const PatchRow *patches,
   const InstRow in = uniform_row(inst[pr.inst]);
   const Coef<double> k = make_coef<double>(in.c, in.Z, dt, pr.dx, pr.dy);
   const int l = (int)threadIdx.x;
+  // the lane's first receiver, loaded ahead of the march
+  const bool adds = add.n > 0 && (int)blockIdx.y == add.patch;
+  int ai = -1, aj = -1;
+  if (adds && l < add.n) ai = add.ij[2 * l], aj = add.ij[2 * l + 1];
   AdjLanes M;
   const int64_t org = pr.q_off + pr.col0 - 2;  // padded cell (-2, -2)
   M.lb = reinterpret_cast<const char *>(lam_in + org);
@@ -281,6 +287,17 @@ __global__ __launch_bounds__(64) void adjoint_kernel(const PatchRow *patches,
   const bool fold = pr.bc == WS_BC_EXTRAP;
   const bool xedge = tx == 0 || tx == ntx - 1;
   adjoint_march(M, k, l, r0 == 0 ? -2 : r0, r1 == pr.my ? pr.my + 2 : r1, fold, xedge);
+  if (!adds) return;
+  const int c0 = tx * 60, c1 = min(c0 + 60, pr.mx);
+  for (int n = l; n < add.n; n += 64) {
+    if (n != l) ai = add.ij[2 * n], aj = add.ij[2 * n + 1];
+    if (ai >= c0 && ai < c1 && aj >= r0 && aj < r1) {
+      // the wavefront's stores are complete (several lanes may hold one cell)
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+      atomicAdd(&lam_out[pr.q_off + add.comp * pr.plane + (int64_t)(aj + 2) * pr.ld + pr.col0 + ai],
+                add.val[n]);
+    }
+  }
 }
 
 __global__ void gather_kernel(const PatchRow *patches, int patch, int comp, int n,
@@ -309,7 +326,8 @@ __global__ void add_at_kernel(const PatchRow *patches, int patch, int comp, int 
 
 hipError_t launch_adjoint(const PatchRow *patches, int n_patches, int max_mx, int max_my,
                           int n_cu, const InstRow *inst, double dt, const uint8_t *masks,
-                          const double *lam_in, double *lam_out, hipStream_t s) {
+                          const double *lam_in, double *lam_out, const AdjointAdd &add,
+                          hipStream_t s) {
   if (n_patches <= 0) return hipSuccess;
   // rows per segment: the tallest of 32, 16, 8, 4, 2 that still gives
   // WS_ADJ_WAVES_PER_CU wavefronts per CU (a small level is worked by many
@@ -321,7 +339,7 @@ hipError_t launch_adjoint(const PatchRow *patches, int n_patches, int max_mx, in
     rows /= 2;
   const int nty = (max_my + rows - 1) / rows;
   hipLaunchKernelGGL(adjoint_kernel, dim3((unsigned)(ntx * nty), (unsigned)n_patches), dim3(64),
-                     0, s, patches, inst, dt, masks, lam_in, lam_out, rows);
+                     0, s, patches, inst, dt, masks, lam_in, lam_out, rows, add);
   return hipGetLastError();
 }
 

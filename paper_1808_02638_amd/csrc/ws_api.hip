@@ -53,6 +53,9 @@ int fail(int code, const char *fmt, ...) {
 int64_t round_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 bool same_rel(double a, double b) { return std::fabs(a - b) <= 1e-12 * std::fabs(b); }
 
+// Receivers an adjoint step adds itself (one look per lane and 64 of them).
+constexpr int kMaxFusedAdds = 256;
+
 constexpr int kTileWidths[] = {8, 16, 32, 64, 128, 256};
 
 struct PoolLayout {
@@ -205,6 +208,32 @@ void default_tile(int mx, int my, int bc, int n_cu, int *variant, int *tw, int *
   *th = nty * r;
 }
 
+// A level whose default tiles leave much of the GPU idle is bound by one
+// segment's march, so its MARCH segments get shorter: 8 or 4 rows while the
+// workgroups stay within a round and a quarter of the places (four per CU),
+// 2 or 1 only while a sixteenth of the places is taken (a segment loads ten
+// rows whatever its height).  Steps of one FP64 patch back to back, us: 64^2
+// 9.3 with 16 rows, 5.2 with 4, 4.3 with 1; 201 x 147 16.4, 5.3 and 6.4;
+// 512^2 9.6 with 16, 7.0 with 8, 6.5 with 4, 7.3 with 2, 9.3 with 1; 1024^2
+// 14.0 with 16, 12.6 with 8, 12.0 with 4, 16.3 with 2.  Only powers of two:
+// heights between them measured slower than both.
+void short_segments(std::vector<PatchRow> &rows, int n_cu) {
+  auto count = [&](int seg) {
+    int64_t n = 0;
+    for (const PatchRow &r : rows) {
+      const int th = r.variant == kMarch ? std::min(r.th, 4 * seg) : r.th;
+      n += tiles_of(r.mx, r.my, r.variant, r.tw, th);
+    }
+    return n;
+  };
+  const int64_t places = 4 * (int64_t)std::max(n_cu, 1);
+  int seg = 16;
+  while (seg > 1 && count(seg / 2) <= (seg > 4 ? places + places / 4 : places / 16)) seg /= 2;
+  if (seg == 16) return;
+  for (PatchRow &r : rows)
+    if (r.variant == kMarch) r.th = std::min(r.th, 4 * seg);
+}
+
 // MARCH tiles address a patch with 32-bit byte offsets (all three planes).
 bool march_fits(int64_t plane, int dtype) {
   return 3 * plane * (dtype == WS_F32 ? 4 : 8) < (int64_t{1} << 31);
@@ -320,6 +349,13 @@ struct ws_ctx {
     a.masks = nullptr;
     a.medium = medium;
     return a;
+  }
+
+  // The two-step launch's tiles.
+  void two_args(StepArgs &a) const {
+    a.tiles = d_tiles() + tiles.size();
+    a.n_tiles = (int32_t)two_tiles.size();
+    a.seg_rows = two_rows;
   }
 
   void drop_graph() {
@@ -512,6 +548,7 @@ static int setup_level(ws_ctx *c, const ws_patch_desc *patches, int32_t n_patche
     c->max_mx = std::max(c->max_mx, d.mx);
     c->max_my = std::max(c->max_my, d.my);
   }
+  short_segments(c->rows, c->n_cu);
   c->mask_total = mask_off;
   sum_tiles(c->rows, c->stiles);
   c->order.resize(n_patches);
@@ -629,10 +666,13 @@ int ws_attach_medium(ws_ctx *c, void *medium, int64_t bytes) {
   }
   HIPCHK(hipStreamSynchronize(c->stream));
   c->medium = medium;
-  // DIRECT tiles (the default DIRECT shape of each patch)
+  // MARCH tiles where a patch fills a segment's columns, else the default
+  // DIRECT shape.  2048^2 FP64: 81 us per step with the MARCH default, 146
+  // with the DIRECT one.
   for (int k = 0; k < c->n_patches; ++k) {
     PatchRow &r = c->rows[k];
-    default_tile(r.mx, r.my, WS_BC_PERIODIC, c->n_cu, &r.variant, &r.tw, &r.th);
+    const bool march = r.mx >= kMarchWidth - 4 && march_fits(r.plane, c->dtype);
+    default_tile(r.mx, r.my, march ? r.bc : WS_BC_PERIODIC, c->n_cu, &r.variant, &r.tw, &r.th);
   }
   c->drop_graph();
   return c->build_tiles();
@@ -848,6 +888,20 @@ static int read_level_cfl(ws_ctx *c, double *cfl_out) {
   return WS_OK;
 }
 
+// The Courant number of a homogeneous level's step with one dt, as the step
+// files it (the same operations in the same precision), after the step.
+static int closed_level_cfl(ws_ctx *c, double dt, double *cfl_out) {
+  if (!cfl_out) return WS_OK;
+  double lvl = 0.0;
+  for (int k = 0; k < c->n_inst; ++k) {
+    const double cs = c->inst_host[k].c;
+    lvl = std::fmax(lvl, std::fmax(cs * (dt / c->min_host[k].dx), cs * (dt / c->min_host[k].dy)));
+  }
+  HIPCHK(hipStreamSynchronize(c->stream));
+  *cfl_out = lvl;
+  return WS_OK;
+}
+
 int ws_step_level(ws_ctx *c, double dt, double *cfl_out) {
   if (!c) return fail(WS_EINVAL, "ctx is NULL");
   if (!(dt > 0.0) || !std::isfinite(dt)) return fail(WS_EINVAL, "dt must be finite and > 0");
@@ -856,7 +910,7 @@ int ws_step_level(ws_ctx *c, double dt, double *cfl_out) {
   HIPCHK(launch_step(c->dtype, c->lim_code(), c->vars, a, c->grid, c->stream));
   if (int rc = link_after_step(c, 1 - c->cur)) return rc;
   c->cur = 1 - c->cur;
-  return read_level_cfl(c, cfl_out);
+  return c->medium ? read_level_cfl(c, cfl_out) : closed_level_cfl(c, dt, cfl_out);
 }
 
 int ws_step_level_per_patch(ws_ctx *c, double dt, double *cfl_out) {
@@ -899,9 +953,7 @@ static int enqueue_auto(ws_ctx *c, int src, double cfl_desired) {
 // Two steps in one launch, from pool `src` into the other.
 static int enqueue_two(ws_ctx *c, int src, double cfl_desired) {
   StepArgs a = c->step_args(src, 0.0, cfl_desired);
-  a.tiles = c->d_tiles() + c->tiles.size();
-  a.n_tiles = (int32_t)c->two_tiles.size();
-  a.seg_rows = c->two_rows;
+  c->two_args(a);
   HIPCHK(launch_step_two(c->dtype, c->limiter, a, c->stream));
   return WS_OK;
 }
@@ -1087,15 +1139,16 @@ static int check_adjoint_ctx(ws_ctx *c) {
   return WS_OK;
 }
 
-int ws_adjoint_step(ws_ctx *c, double dt, const void *masks_dev, const void *lam_in,
-                    void *lam_out) {
+// What ws_adjoint_step and ws_adjoint_sweep require of the level.
+static int check_adjoint_level(ws_ctx *c, double dt, const void *masks, const void *lam_a,
+                               const void *lam_b) {
   if (int rc = check_adjoint_ctx(c)) return rc;
   if (c->limiter != WS_LIM_MC || c->medium)
     return fail(WS_EINVAL,
                 "the adjoint needs the MC limiter of the default variant in a homogeneous medium");
   if (c->link_src) return fail(WS_EINVAL, "the adjoint does not take a tiled level");
-  if (!masks_dev || !lam_in || !lam_out) return fail(WS_EINVAL, "NULL buffer");
-  if (lam_in == lam_out) return fail(WS_EINVAL, "lam_in and lam_out must be distinct buffers");
+  if (!masks || !lam_a || !lam_b) return fail(WS_EINVAL, "NULL buffer");
+  if (lam_a == lam_b) return fail(WS_EINVAL, "lam_in and lam_out must be distinct buffers");
   if (!(dt > 0.0) || !std::isfinite(dt)) return fail(WS_EINVAL, "dt must be finite and > 0");
   for (int k = 0; k < c->n_patches; ++k)
     if (c->rows[k].bc == WS_BC_PERIODIC)
@@ -1103,12 +1156,23 @@ int ws_adjoint_step(ws_ctx *c, double dt, const void *masks_dev, const void *lam
   for (int k = 0; k < c->n_patches; ++k)
     if (!march_fits(c->rows[k].plane, WS_F64))
       return fail(WS_EINVAL, "patch %d: too large for the adjoint (32-bit offsets)", k);
+  return WS_OK;
+}
+
+static int enqueue_adjoint(ws_ctx *c, double dt, const void *masks, const void *lam_in,
+                           void *lam_out, const AdjointAdd &add) {
   HIPCHK(launch_adjoint(c->d_patches(), c->n_patches, c->max_mx, c->max_my, c->n_cu,
                         reinterpret_cast<const InstRow *>(c->ws + c->L.inst), dt,
-                        reinterpret_cast<const uint8_t *>(masks_dev),
+                        reinterpret_cast<const uint8_t *>(masks),
                         reinterpret_cast<const double *>(lam_in),
-                        reinterpret_cast<double *>(lam_out), c->stream));
+                        reinterpret_cast<double *>(lam_out), add, c->stream));
   return WS_OK;
+}
+
+int ws_adjoint_step(ws_ctx *c, double dt, const void *masks_dev, const void *lam_in,
+                    void *lam_out) {
+  if (int rc = check_adjoint_level(c, dt, masks_dev, lam_in, lam_out)) return rc;
+  return enqueue_adjoint(c, dt, masks_dev, lam_in, lam_out, AdjointAdd{});
 }
 
 static int check_cells(ws_ctx *c, int32_t patch, int32_t comp, int32_t n, const void *ij,
@@ -1136,6 +1200,71 @@ int ws_add_at(ws_ctx *c, void *buf, int32_t patch, int32_t comp, int32_t n, cons
   void *dst = buf ? buf : c->pool[c->cur];
   HIPCHK(launch_add_at(c->d_patches(), patch, comp, n, ij, val, reinterpret_cast<double *>(dst),
                        c->stream));
+  return WS_OK;
+}
+
+int ws_step_traces(ws_ctx *c, int32_t n_steps, double dt, int32_t patch, int32_t n,
+                   const int32_t *ij, double *traces, void *masks_dev, int64_t mask_stride,
+                   int32_t last_alone) {
+  if (int rc = check_cells(c, patch, 0, n, ij, traces)) return rc;
+  if (n_steps < 1) return fail(WS_EINVAL, "n_steps must be >= 1");
+  if (!(dt > 0.0) || !std::isfinite(dt)) return fail(WS_EINVAL, "dt must be finite and > 0");
+  if (masks_dev && mask_stride < c->mask_total)
+    return fail(WS_EINVAL, "mask_stride is below ws_mask_bytes");
+  uint8_t *masks = reinterpret_cast<uint8_t *>(masks_dev);
+  const bool pair = !c->two_tiles.empty() && !c->link_src &&
+                    (!masks || (c->limiter == WS_LIM_MC && !(c->vars & 4)));
+  const int pairs = !pair ? 0 : last_alone ? (n_steps - 1) / 2 : n_steps / 2;
+  int step = 0;
+  for (int k = 0; k < pairs; ++k, step += 2) {
+    StepArgs a = c->step_args(c->cur, dt, 0.0);
+    c->two_args(a);
+    if (masks) a.masks = masks + step * mask_stride, a.masks2 = a.masks + mask_stride;
+    a.rec_patch = patch;
+    a.rec_n = n;
+    a.rec_ij = ij;
+    a.rec_now = step > 0 ? traces + (int64_t)(step - 1) * n : nullptr;
+    a.rec_mid = traces + (int64_t)step * n;
+    HIPCHK(launch_step_two(c->dtype, c->limiter, a, c->stream));
+    c->cur = 1 - c->cur;
+  }
+  if (step > 0)
+    if (int rc = ws_gather(c, nullptr, patch, 0, n, ij, traces + (int64_t)(step - 1) * n)) return rc;
+  for (; step < n_steps; ++step) {
+    if (int rc = masks ? ws_step_record_masks(c, dt, masks + step * mask_stride, nullptr)
+                       : ws_step_level(c, dt, nullptr))
+      return rc;
+    if (int rc = ws_gather(c, nullptr, patch, 0, n, ij, traces + (int64_t)step * n)) return rc;
+  }
+  return WS_OK;
+}
+
+int ws_adjoint_sweep(ws_ctx *c, int32_t n_steps, double dt, const void *masks_dev,
+                     int64_t mask_stride, int32_t patch, int32_t n, const int32_t *ij,
+                     const double *g, int32_t add_first, int32_t add_before, void *lam_a,
+                     void *lam_b) {
+  if (int rc = check_adjoint_level(c, dt, masks_dev, lam_a, lam_b)) return rc;
+  if (int rc = check_cells(c, patch, 0, n, ij, g)) return rc;
+  if (n_steps < 1) return fail(WS_EINVAL, "n_steps must be >= 1");
+  if (mask_stride < c->mask_total) return fail(WS_EINVAL, "mask_stride is below ws_mask_bytes");
+  const uint8_t *masks = reinterpret_cast<const uint8_t *>(masks_dev);
+  void *lam[2] = {lam_a, lam_b};
+  // every wavefront of an adjoint step looks through the receivers, so many
+  // of them are added by a launch of their own
+  const bool fused = n <= kMaxFusedAdds;
+  if (add_first)
+    if (int rc = ws_add_at(c, lam[0], patch, 0, n, ij, g + (int64_t)(n_steps - 1) * n)) return rc;
+  int cur = 0;
+  for (int step = n_steps - 1; step >= 0; --step, cur = 1 - cur) {
+    const bool more = step > 0 || add_before;
+    const double *next = g + (int64_t)(step - 1) * n;
+    AdjointAdd add{};
+    if (more && fused) add = AdjointAdd{patch, 0, n, ij, next};
+    if (int rc = enqueue_adjoint(c, dt, masks + step * mask_stride, lam[cur], lam[1 - cur], add))
+      return rc;
+    if (more && !fused)
+      if (int rc = ws_add_at(c, lam[1 - cur], patch, 0, n, ij, next)) return rc;
+  }
   return WS_OK;
 }
 

@@ -44,7 +44,13 @@ struct StepArgs {
   unsigned int *retire;  // (kGroups + 1) counters, kLine apart
   uint8_t *masks;        // nullptr unless the branches are recorded
   const void *medium;    // nullptr, or per-cell (c, Z) planes laid out like a q pool
-  int32_t seg_rows;      // two-step launch: rows per segment
+  // two-step launch only
+  int32_t seg_rows;      // rows per segment
+  uint8_t *masks2;       // branches of the second step (masks: of the first)
+  int32_t rec_patch, rec_n;  // receivers: cells of one patch, FP64 levels only
+  const int32_t *rec_ij;
+  double *rec_now;       // nullptr, or p at them before the first step
+  double *rec_mid;       // and after it
 };
 
 // Bit OR-ed into the limiter code of the kernel launchers when the level has a
@@ -58,8 +64,8 @@ hipError_t launch_step(int dtype, int limiter, int vars, const StepArgs &a, int 
                        hipStream_t s);
 // Two steps in one launch (ws_multi.hip): homogeneous levels whose patches all
 // have extrapolation boundaries, default transverse variant; a.tiles are
-// kMultiCols columns by 4 seg_rows rows, a.cfl_desired > 0 rescales dt after
-// each of the two steps.
+// kMultiCols columns by 4 seg_rows rows; a.dt_override > 0 fixes dt, else
+// a.cfl_desired > 0 rescales it after each of the two steps.
 hipError_t launch_step_two(int dtype, int limiter, const StepArgs &a, hipStream_t s);
 // Workgroups of that launch a CU holds at once (0: unknown).
 int step_two_occupancy(int dtype, int limiter);
@@ -103,11 +109,18 @@ int step_occupancy(int dtype, int limiter, int vars, int *wg_per_cu);
 
 // Adjoint and receiver helpers (defined in ws_adjoint.hip), FP64 buffers in
 // the pools' layout.
-// lam_out <- E^T U^T lam_in (one launch: the gather-form update transpose
+// Values added to a cotangent at n cells (i, j) of one component of a patch.
+struct AdjointAdd {
+  int32_t patch, comp, n;
+  const int32_t *ij;
+  const double *val;
+};
+// lam_out <- E^T U^T lam_in, plus add at its cells (one launch: the gather-form update transpose
 // with the extrapolation ghosts folded into the boundary cells).
 hipError_t launch_adjoint(const PatchRow *patches, int n_patches, int max_mx, int max_my,
                           int n_cu, const InstRow *inst, double dt, const uint8_t *masks,
-                          const double *lam_in, double *lam_out, hipStream_t s);
+                          const double *lam_in, double *lam_out, const AdjointAdd &add,
+                          hipStream_t s);
 hipError_t launch_gather(const PatchRow *patches, int patch, int comp, int n, const int32_t *ij,
                          const double *buf, double *out, hipStream_t s);
 hipError_t launch_add_at(const PatchRow *patches, int patch, int comp, int n, const int32_t *ij,

@@ -44,16 +44,6 @@
 namespace ws {
 namespace {
 
-// MC branch taken: 0 -> 0, 1 -> (a+b)/2, 2 -> 2a, 3 -> 2b; ties -> lowest.
-template <typename T>
-__device__ inline unsigned mc_branch(T a, T b) {
-  const bool same = (a > T(0) && b > T(0)) || (a < T(0) && b < T(0));
-  if (!same) return 0u;
-  const T m1 = fabs(a + b) * T(0.5), m2 = fabs(a) * T(2), m3 = fabs(b) * T(2);
-  if (m1 <= m2 && m1 <= m3) return 1u;
-  return (m2 <= m3) ? 2u : 3u;
-}
-
 // Transverse-correction variant: the split vectors are the fluctuations with
 // the limited correction moved into them, A+dQ - 2 Fc at a cell's left edge
 // and A-dQ + 2 Fc at its right edge.  Only their p parts reach the split, so
@@ -68,16 +58,6 @@ template <typename T>
 __device__ inline T moved(T xs, T t, T d_lo, T d_hi) {
   return xs + t * (d_hi - d_lo);
 }
-
-// Padded planes of one patch, indexed by interior coordinates (i, j).
-template <typename T>
-struct Planes {
-  const T *p, *u, *v;
-  int64_t ld;
-  __device__ T P(int i, int j) const { return p[(int64_t)j * ld + i]; }
-  __device__ T U(int i, int j) const { return u[(int64_t)j * ld + i]; }
-  __device__ T V(int i, int j) const { return v[(int64_t)j * ld + i]; }
-};
 
 // The same planes read through unsigned 32-bit byte offsets from a
 // wave-uniform base at padded cell (-2, -2) of plane 0: each load takes the
@@ -96,65 +76,6 @@ struct Planes32 {
     return *reinterpret_cast<const T *>(b + 2 * plb + off(i, j));
   }
 };
-
-struct CellMasks {
-  unsigned own;    // bits of the cell's left x-edge (0-3) and bottom y-edge (4-7)
-  unsigned right;  // bits 0-3 of the right x-edge (stored at cell i+1)
-  unsigned top;    // bits 4-7 of the top y-edge (stored at cell j+1)
-};
-
-// DIRECT path: the whole update of one interior cell from its 13-point
-// footprint.
-template <typename T, int LIM, bool MASKS>
-__device__ __attribute__((always_inline)) inline void cell_update(const Planes<T> &q, int i, int j, const Coef<T> &k, T &pn,
-                                   T &un, T &vn, CellMasks *mk) {
-  const T Z = k.Z;
-  // ---- x-edges of row j: LL = i-3/2, L = i-1/2, R = i+1/2, RR = i+3/2
-  const T pm2 = q.P(i - 2, j), pm1 = q.P(i - 1, j), p0 = q.P(i, j), pp1 = q.P(i + 1, j),
-          pp2 = q.P(i + 2, j);
-  const T um2 = q.U(i - 2, j), um1 = q.U(i - 1, j), u0 = q.U(i, j), up1 = q.U(i + 1, j),
-          up2 = q.U(i + 2, j);
-  const T a2LL = s2(Z, pm1 - pm2, um1 - um2);
-  const T a1L = s1(Z, p0 - pm1, u0 - um1), a2L = s2(Z, p0 - pm1, u0 - um1);
-  const T a1R = s1(Z, pp1 - p0, up1 - u0), a2R = s2(Z, pp1 - p0, up1 - u0);
-  const T a1RR = s1(Z, pp2 - pp1, up2 - up1);
-  // ---- y-edges of column i: BB = j-3/2, B = j-1/2, T = j+1/2, TT = j+3/2
-  const T qm2 = q.P(i, j - 2), qm1 = q.P(i, j - 1), qp1 = q.P(i, j + 1), qp2 = q.P(i, j + 2);
-  const T vm2 = q.V(i, j - 2), vm1 = q.V(i, j - 1), v0 = q.V(i, j), vp1 = q.V(i, j + 1),
-          vp2 = q.V(i, j + 2);
-  const T b2BB = s2(Z, qm1 - qm2, vm1 - vm2);
-  const T b1B = s1(Z, p0 - qm1, v0 - vm1), b2B = s2(Z, p0 - qm1, v0 - vm1);
-  const T b1T = s1(Z, qp1 - p0, vp1 - v0), b2T = s2(Z, qp1 - p0, vp1 - v0);
-  const T b1TT = s1(Z, qp2 - qp1, vp2 - vp1);
-
-  // ---- first-order fluctuations entering the cell (and its neighbours)
-  const T xs0 = a2L + a1R, ys0 = b2B + b1T;
-  const T pdm = q.P(i - 1, j - 1), pdp = q.P(i + 1, j - 1);
-  const T udm = q.U(i - 1, j - 1), udp = q.U(i + 1, j - 1);
-  const T xsm = s2(Z, qm1 - pdm, q.U(i, j - 1) - udm) + s1(Z, pdp - qm1, udp - q.U(i, j - 1));
-  const T pum = q.P(i - 1, j + 1), pup = q.P(i + 1, j + 1);
-  const T uum = q.U(i - 1, j + 1), uup = q.U(i + 1, j + 1);
-  const T xsp = s2(Z, qp1 - pum, q.U(i, j + 1) - uum) + s1(Z, pup - qp1, uup - q.U(i, j + 1));
-  const T vlm = q.V(i - 1, j - 1), vl0 = q.V(i - 1, j), vlp = q.V(i - 1, j + 1);
-  const T ysl = s2(Z, pm1 - pdm, vl0 - vlm) + s1(Z, pum - pm1, vlp - vl0);
-  const T vrm = q.V(i + 1, j - 1), vr0 = q.V(i + 1, j), vrp = q.V(i + 1, j + 1);
-  const T ysr = s2(Z, pp1 - pdp, vr0 - vrm) + s1(Z, pup - pp1, vrp - vr0);
-
-  // ---- F~ and G~ on the four edges, then the update
-  T FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2;
-  ftilde<T, LIM>(k, a1L, a2L, a1R, a2LL, ysl, ys0, FL1, FL2);
-  ftilde<T, LIM>(k, a1R, a2R, a1RR, a2L, ys0, ysr, FR1, FR2);
-  gtilde<T, LIM>(k, b1B, b2B, b1T, b2BB, xsm, xs0, GB1, GB2);
-  gtilde<T, LIM>(k, b1T, b2T, b1TT, b2B, xs0, xsp, GT1, GT2);
-  update<T>(k, p0, u0, v0, a2L, a1R, b2B, b1T, FL1, FL2, FR1, FR2, GB1, GB2, GT1, GT2, pn, un, vn);
-
-  if constexpr (MASKS) {
-    mk->own = mc_branch(a1L, a1R) | (mc_branch(a2L, a2LL) << 2) | (mc_branch(b1B, b1T) << 4) |
-              (mc_branch(b2B, b2BB) << 6);
-    mk->right = mc_branch(a1R, a1RR) | (mc_branch(a2R, a2L) << 2);
-    mk->top = (mc_branch(b1T, b1TT) << 4) | (mc_branch(b2T, b2B) << 6);
-  }
-}
 
 // DIRECT path of the transverse-correction variant: the split vectors of the
 // cell and its four neighbours need the limited strengths on both x-edges of

@@ -27,13 +27,14 @@ namespace {
 // What a step carries up its column between rows.
 template <typename T>
 struct Carry {
+  unsigned ybits;        // branches of the row's bottom edge (recording only)
   T yb2, b1h, b2h;       // b2 of the cell's bottom edge; b1, b2 of its top edge
   T GB1, GB2;            // G~ of the bottom edge (characteristic)
   T a1L, a2L;            // strengths of the row's left x-edge
 };
 
 // Carry for row r from rows r-2 (p, v), r-1, r and r+1 (p, v).
-template <typename T, int LIM>
+template <typename T, int LIM, bool MASKS>
 __device__ __attribute__((always_inline)) inline Carry<T> carry_in(const Coef<T> &k,
                                                                    const Row3<T> &M2,
                                                                    const Row3<T> &M1,
@@ -52,16 +53,19 @@ __device__ __attribute__((always_inline)) inline Carry<T> carry_in(const Coef<T>
   S.a1L = s1(Z, A.p - pl, A.u - ul);
   S.a2L = s2(Z, A.p - pl, A.u - ul);
   gtilde<T, LIM>(k, b1m, b2m, S.b1h, b2mm, xsm, S.a2L + shl(S.a1L), S.GB1, S.GB2);
+  if constexpr (MASKS) S.ybits = (mc_branch(b1m, S.b1h) << 4) | (mc_branch(b2m, b2mm) << 6);
   return S;
 }
 
 // The update of row r from rows r (A), r+1 (B) and r+2 (C; p, v); slides the
-// carry up one row.
-template <typename T, int LIM>
+// carry up one row.  branches: those of its left and bottom edges, as a
+// branch byte (recording only).
+template <typename T, int LIM, bool MASKS>
 __device__ __attribute__((always_inline)) inline Row3<T> row_step(const Coef<T> &k, Carry<T> &S,
                                                                   const Row3<T> &A,
                                                                   const Row3<T> &B,
-                                                                  const Row3<T> &C) {
+                                                                  const Row3<T> &C,
+                                                                  unsigned &branches) {
   const T Z = k.Z;
   const T b1hh = s1(Z, C.p - B.p, C.v - B.v), b2hh = s2(Z, C.p - B.p, C.v - B.v);
   const T ys0 = S.yb2 + S.b1h;
@@ -76,6 +80,10 @@ __device__ __attribute__((always_inline)) inline Row3<T> row_step(const Coef<T> 
   Row3<T> N;
   update<T>(k, A.p, A.u, A.v, S.a2L, a1R, S.yb2, S.b1h, FL1, FL2, FR1, FR2, S.GB1, S.GB2, GT1, GT2,
             N.p, N.u, N.v);
+  if constexpr (MASKS) {
+    branches = mc_branch(S.a1L, a1R) | (mc_branch(S.a2L, shr(S.a2L)) << 2) | S.ybits;
+    S.ybits = (mc_branch(S.b1h, b1hh) << 4) | (mc_branch(S.b2h, S.yb2) << 6);
+  }
   S.yb2 = S.b2h, S.b1h = b1hh, S.b2h = b2hh;
   S.GB1 = GT1, S.GB2 = GT2;
   S.a1L = a1Ln, S.a2L = a2Ln;
@@ -108,18 +116,24 @@ struct MultiLanes {
   int my, rmax;          // rmax: last row the segment needs
   int lo, hi;            // lanes of columns 0 and mx-1 (negative, over 63: not in the segment)
   bool glo, ghi;         // the lane holds a ghost column of the low, the high side
+  int i, mx, r0, r1;     // the lane's column; the segment's rows
+  bool own, edge;        // the lane updates its column; holds the one past the last updated
 
-  __device__ MultiLanes(const T *qi, T *qo, const PatchRow &pr, int i0, int l, int r1) {
+  __device__ MultiLanes(const T *qi, T *qo, const PatchRow &pr, int i0, int l, int r0_,
+                        int r1_) {
     constexpr int halo = kMultiHalo;
     ldb = (unsigned)pr.ld * (unsigned)sizeof(T);
     plb = (unsigned)pr.plane * (unsigned)sizeof(T);
     my = pr.my;
+    r0 = r0_;
+    r1 = r1_;
     rmax = min(r1 + 3, pr.my - 1);
     const int64_t first = 2 * (int64_t)pr.ld + 2;
     ib = __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(qi - first), 0, (int)(3 * plb),
                                            kRawBufferWord3);
     ob = __builtin_amdgcn_make_buffer_rsrc(qo - first, 0, (int)(3 * plb), kRawBufferWord3);
-    const int i = i0 + l, mx = pr.mx;
+    i = i0 + l;
+    mx = pr.mx;
     colb = (unsigned)(min(max(i, 0), mx - 1) + 2) * (unsigned)sizeof(T);
     lo = -i0;
     hi = mx - 1 - i0;
@@ -129,6 +143,15 @@ struct MultiLanes {
     const int s = i < 0 ? lo : i >= mx ? hi : l;
     const bool st = i >= -2 && i <= mx + 1 && s >= halo && s < kMarchWidth - halo;
     ocolb = st ? (unsigned)(i + 2) * (unsigned)sizeof(T) : kDropOffset;
+    own = l >= halo && l < kMarchWidth - halo && i < mx;
+    edge = i == mx && l > halo && l <= kMarchWidth - halo;
+  }
+  // The branch byte of row r, and above the last row that of its top edges.
+  __device__ void record(uint8_t *masks, int r, unsigned branches, unsigned top) const {
+    if (r < r0 || r >= r1) return;
+    uint8_t *row = masks + (int64_t)r * (mx + 1) + i;
+    if (own || edge) row[0] = (uint8_t)(own ? branches : branches & 15u);
+    if (r == my - 1 && (own || edge)) row[mx + 1] = (uint8_t)(own ? top : 0u);  // no edge owns the corner
   }
   // Whether the segment holds ghost columns.
   __device__ bool ghosts() const { return lo > 0 || hi < kMarchWidth - 1; }
@@ -169,11 +192,13 @@ struct MultiLanes {
 // its row 0 and those above it of its last row.  The other segments' loop has
 // no branches: a wavefront alone on its SIMD issues one instruction of any
 // kind per four cycles, so what goes into branches and addresses counts.
-template <typename T, int LIM, bool EDGE>
+template <typename T, int LIM, bool EDGE, bool MASKS>
 __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes<T> &M,
                                                                 const Coef<T> &ka,
-                                                                const Coef<T> &kb, int r0,
-                                                                int r1) {
+                                                                const Coef<T> &kb,
+                                                                uint8_t *masks,
+                                                                uint8_t *masks2) {
+  const int r0 = M.r0, r1 = M.r1;
   const bool bottom = EDGE && r0 == 0;
   Row3<T> R[kMultiSets], W[3], M2, M1, e0, e1;
   const int q0 = bottom ? 0 : r0 - 2;  // first row of the first step
@@ -187,25 +212,27 @@ __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes
   M.fetch(R[4], r0 + 2);
   M.fetch(R[5], r0 + 3);
   Carry<T> S, S2;
-  // the first step's row from sets A, B, C; A is refilled
-  auto first = [&](Row3<T> &A, const Row3<T> &B, const Row3<T> &C, int next) {
-    Row3<T> N = row_step<T, LIM>(ka, S, A, B, C);
+  // the first step's row r from sets A, B, C; A is refilled
+  auto first = [&](Row3<T> &A, const Row3<T> &B, const Row3<T> &C, int r) {
+    unsigned br = 0;
+    Row3<T> N = row_step<T, LIM, MASKS>(ka, S, A, B, C, br);
+    if constexpr (MASKS) M.record(masks, r, br, S.ybits);
     if constexpr (EDGE) M.ghost_columns(N);
-    M.fetch(A, next);
+    M.fetch(A, r + kMultiSets);
     return N;
   };
   if (!bottom) {
-    S = carry_in<T, LIM>(ka, M2, M1, R[0], R[1]);
-    e0 = first(R[0], R[1], R[2], r0 + 4);
-    e1 = first(R[1], R[2], R[3], r0 + 5);
+    S = carry_in<T, LIM, MASKS>(ka, M2, M1, R[0], R[1]);
+    e0 = first(R[0], R[1], R[2], r0 - 2);
+    e1 = first(R[1], R[2], R[3], r0 - 1);
   } else {
-    S = carry_in<T, LIM>(ka, M2, M1, R[2], R[3]);
+    S = carry_in<T, LIM, MASKS>(ka, M2, M1, R[2], R[3]);
   }
-  W[0] = first(R[2], R[3], R[4], r0 + 6);
+  W[0] = first(R[2], R[3], R[4], r0);
   if (bottom) e0 = W[0], e1 = W[0];
-  W[1] = first(R[3], R[4], R[5], r0 + 7);
+  W[1] = first(R[3], R[4], R[5], r0 + 1);
   if (EDGE && r0 + 1 >= M.my) W[1] = W[0];
-  S2 = carry_in<T, LIM>(kb, e0, e1, W[0], W[1]);
+  S2 = carry_in<T, LIM, MASKS>(kb, e0, e1, W[0], W[1]);
 
   // offsets of the row stored and of the row fetched next
   unsigned oo = (unsigned)(r0 + 2) * M.ldb, oi = M.row_offset(r0 + 8);
@@ -213,7 +240,9 @@ __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes
   auto row = [&](Row3<T> &A, const Row3<T> &B, const Row3<T> &C, const Row3<T> &Wa,
                  const Row3<T> &Wb, Row3<T> &Wc, int r) {
     __builtin_amdgcn_sched_barrier(0);
-    Wc = row_step<T, LIM>(ka, S, A, B, C);
+    unsigned br = 0;
+    Wc = row_step<T, LIM, MASKS>(ka, S, A, B, C, br);
+    if constexpr (MASKS) M.record(masks, r + 2, br, S.ybits);
     if constexpr (EDGE) {
       M.ghost_columns(Wc);
       if (r + 2 >= M.my) {
@@ -222,7 +251,8 @@ __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes
       }
     }
     __builtin_amdgcn_sched_barrier(0);
-    Row3<T> N = row_step<T, LIM>(kb, S2, Wa, Wb, Wc);
+    Row3<T> N = row_step<T, LIM, MASKS>(kb, S2, Wa, Wb, Wc, br);
+    if constexpr (MASKS) M.record(masks2, r, br, S2.ybits);
     if constexpr (EDGE) {
       M.ghost_columns(N);
       if (r == 0) M.put_at(N, 0), M.put_at(N, M.ldb);
@@ -255,7 +285,31 @@ __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes
 __device__ inline double next_dt(double dt, double c, const InstMin &m, double cfl_desired,
                                  double &cfl) {
   cfl = fmax(c * (dt / m.dx), c * (dt / m.dy));
-  return cfl > 0.0 ? dt * cfl_desired / cfl : dt;
+  return cfl_desired > 0.0 && cfl > 0.0 ? dt * cfl_desired / cfl : dt;
+}
+
+// Receivers: p before the launch's first step, read, and after it, from the
+// cell's 13-point footprint (cell_update, whose bits are the sweep's).  The
+// state after the second step is the next launch's first.
+template <typename T, int LIM>
+__device__ inline void gather_receivers(const StepArgs &a, int first) {
+  const int n = first + (int)threadIdx.x;
+  if (n >= a.rec_n) return;
+  const PatchRow pr = a.patches[a.rec_patch];
+  const int i = a.rec_ij[2 * n], j = a.rec_ij[2 * n + 1];
+  double now = __builtin_nan(""), mid = now;
+  if (i >= 0 && i < pr.mx && j >= 0 && j < pr.my) {
+    const T *q = reinterpret_cast<const T *>(a.qin) + pr.q_off + 2 * (int64_t)pr.ld + pr.col0;
+    const InstRow in = a.inst[pr.inst];
+    const double dt = a.dt_override > 0.0 ? a.dt_override : a.dt[pr.inst];
+    const Coef<T> k = make_coef<T, LIM>(in.c, in.Z, dt, pr.dx, pr.dy);
+    const Planes<T> Q{q, q + pr.plane, q + 2 * pr.plane, pr.ld};
+    T pn, un, vn;
+    cell_update<T, LIM, false>(Q, i, j, k, pn, un, vn, nullptr);
+    now = (double)Q.P(i, j), mid = (double)pn;
+  }
+  if (a.rec_now) a.rec_now[n] = now;
+  a.rec_mid[n] = mid;
 }
 
 // Measured on 2048 x 2048 (200 MB of state, within the Infinity Cache): FP64
@@ -269,22 +323,29 @@ __device__ inline double next_dt(double dt, double c, const InstMin &m, double c
 // wavefront, stacked up the patch.  Workgroups are dispatched round-robin
 // over the XCDs; each XCD takes a contiguous run of tiles, whose halos
 // overlap.  The last workgroup files the two steps' Courant numbers.
-// Wavefronts per SIMD the registers are kept for: three (155 registers in
-// FP64 with the MC limiter; four spilled and ran 4x slower), but two for van
-// Leer in FP64, whose divisions spilled at three.
-template <typename T, int LIM>
+// Wavefronts per SIMD the registers are kept for: three (153 registers in
+// FP64; four spilled and ran 4x slower), two where branches are recorded
+// (197).
+template <typename T, int LIM, bool MASKS>
 constexpr int two_waves() {
-  return sizeof(T) == 8 && LIM == WS_LIM_VANLEER ? 2 : 3;
+  return sizeof(T) == 8 && MASKS ? 2 : 3;
 }
 
-template <typename T, int LIM>
-__global__ __launch_bounds__(kThreads, (two_waves<T, LIM>())) void step_kernel_two(StepArgs a) {
-  if (blockIdx.x == gridDim.x - 1) {
+template <typename T, int LIM, bool MASKS>
+__global__ __launch_bounds__(kThreads, (two_waves<T, LIM, MASKS>())) void step_kernel_two(StepArgs a) {
+  const int work = (a.n_tiles + kGroups - 1) / kGroups * kGroups;  // workgroups of the tiles
+  if ((int)blockIdx.x >= work) {
+    if ((int)blockIdx.x > work) {
+      if constexpr (sizeof(T) == 8)
+        gather_receivers<T, LIM>(a, ((int)blockIdx.x - work - 1) * kThreads);
+      return;
+    }
     const CflSlots &c = a.slots;
     for (int k = (int)threadIdx.x; k < c.n_inst; k += kThreads) {
       const InstMin m = c.inst_min[k];
+      const double dt0 = a.dt_override > 0.0 ? a.dt_override : a.dt[k];
       double cfl0, cfl1;
-      const double dt1 = next_dt(a.dt[k], a.inst[k].c, m, a.cfl_desired, cfl0);
+      const double dt1 = next_dt(dt0, a.inst[k].c, m, a.cfl_desired, cfl0);
       c.dt[k] = next_dt(dt1, a.inst[k].c, m, a.cfl_desired, cfl1);
       c.cfl_last[k] = cfl1;
       c.cfl_max[k] = fmax(fmax(c.cfl_max[k], cfl0), cfl1);
@@ -302,7 +363,7 @@ __global__ __launch_bounds__(kThreads, (two_waves<T, LIM>())) void step_kernel_t
   if (r0 >= r1) return;
   const InstRow in = uniform_row(a.inst[pr.inst]);
   const InstMin m = uniform_row(a.slots.inst_min[pr.inst]);
-  const double dt0 = a.dt[pr.inst];
+  const double dt0 = a.dt_override > 0.0 ? a.dt_override : a.dt[pr.inst];
   double cfl;
   const double dt1 = next_dt(dt0, in.c, m, a.cfl_desired, cfl);
   const Coef<T> ka = make_coef<T, LIM>(in.c, in.Z, dt0, pr.dx, pr.dy);
@@ -310,42 +371,54 @@ __global__ __launch_bounds__(kThreads, (two_waves<T, LIM>())) void step_kernel_t
   const int64_t org = pr.q_off + 2 * (int64_t)pr.ld + pr.col0;
   const MultiLanes<T> M(reinterpret_cast<const T *>(a.qin) + org,
                         reinterpret_cast<T *>(a.qout) + org, pr,
-                        te.tx * kMultiCols - kMultiHalo, (int)threadIdx.x & 63, r1);
+                        te.tx * kMultiCols - kMultiHalo, (int)threadIdx.x & 63, r0, r1);
+  uint8_t *m1 = MASKS ? a.masks + pr.mask_off : nullptr;
+  uint8_t *m2 = MASKS ? a.masks2 + pr.mask_off : nullptr;
   if (M.ghosts() || r0 == 0 || r1 + 2 > pr.my)
-    march_two<T, LIM, true>(M, ka, kb, r0, r1);
+    march_two<T, LIM, true, MASKS>(M, ka, kb, m1, m2);
   else
-    march_two<T, LIM, false>(M, ka, kb, r0, r1);
+    march_two<T, LIM, false, MASKS>(M, ka, kb, m1, m2);
+}
+
+template <typename T, int LIM>
+hipError_t two_l(const StepArgs &a, hipStream_t s) {
+  // the XCDs' runs differ by at most one tile: the grid covers the longest on
+  // each; the filing workgroup and the receivers' come after them
+  const dim3 grid((unsigned)((a.n_tiles + kGroups - 1) / kGroups * kGroups + 1 +
+                             (a.rec_n + kThreads - 1) / kThreads));
+  if constexpr (sizeof(T) == 8 && LIM == WS_LIM_MC) {
+    if (a.masks) {
+      hipLaunchKernelGGL((step_kernel_two<T, LIM, true>), grid, dim3(kThreads), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  if (a.masks) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((step_kernel_two<T, LIM, false>), grid, dim3(kThreads), 0, s, a);
+  return hipGetLastError();
 }
 
 template <typename T>
 hipError_t two_t(int limiter, const StepArgs &a, hipStream_t s) {
-  // the XCDs' runs differ by at most one tile: the grid covers the longest on
-  // each, and the filing workgroup comes after them
-  const dim3 grid((unsigned)((a.n_tiles + kGroups - 1) / kGroups * kGroups + 1)), block(kThreads);
   switch (limiter) {
-    case WS_LIM_NONE:
-      hipLaunchKernelGGL((step_kernel_two<T, WS_LIM_NONE>), grid, block, 0, s, a);
-      break;
-    case WS_LIM_VANLEER:
-      hipLaunchKernelGGL((step_kernel_two<T, WS_LIM_VANLEER>), grid, block, 0, s, a);
-      break;
-    default:
-      hipLaunchKernelGGL((step_kernel_two<T, WS_LIM_MC>), grid, block, 0, s, a);
+    case WS_LIM_NONE: return two_l<T, WS_LIM_NONE>(a, s);
+    case WS_LIM_VANLEER: return two_l<T, WS_LIM_VANLEER>(a, s);
+    default: return two_l<T, WS_LIM_MC>(a, s);
   }
-  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_step_two(int dtype, int limiter, const StepArgs &a, hipStream_t s) {
   if (a.n_tiles <= 0 || a.seg_rows <= 0) return hipErrorInvalidValue;
+  if (a.rec_n > 0 && dtype != WS_F64) return hipErrorInvalidValue;
   return dtype == WS_F32 ? two_t<float>(limiter, a, s) : two_t<double>(limiter, a, s);
 }
 
 template <typename T, int LIM>
 static int two_occupancy_of() {
   int n = 0;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel_two<T, LIM>, kThreads, 0) ==
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel_two<T, LIM, false>,
+                                                      kThreads, 0) ==
                  hipSuccess
              ? n
              : 0;

@@ -7,6 +7,7 @@ single steps, bit for bit, at the edges of the pairing (1 .. 8 steps), of the
 56-column segments and of the rows that a segment shares with its neighbours.
 """
 
+import ctypes
 import math
 
 import numpy as np
@@ -14,6 +15,13 @@ import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ws():
+    import paper_1808_02638_amd as m
+
+    return m
 
 
 def _pair(ws, sizes, dtype, limiter):
@@ -68,3 +76,46 @@ def test_every_remainder_of_the_pairing(ws, n):
     for _ in range(n):
         b.step_auto(0.9)
     _same(a, b)
+
+
+@pytest.mark.parametrize("n_steps,last", [(1, 0), (2, 0), (2, 1), (5, 0), (6, 1)])
+@pytest.mark.parametrize("shape,nr", [((61, 9), 7), ((130, 77), 70), ((57, 40), 300)])
+def test_traces_branches_and_sweep(ws, shape, nr, n_steps, last):
+    """ws_step_traces and ws_adjoint_sweep against single calls, bit for bit."""
+    mx, my = shape
+    C = ws._lib
+    L = C.lib()
+    (a, b) = _pair(ws, [(mx, my)], torch.float64, "mc")
+    dt = 0.4 * min(1 / mx, 1.3 / my) / 2.0
+    at = np.random.default_rng(3).choice(mx * my, nr, replace=False)
+    ij = torch.tensor(np.stack([at % mx, at // mx], 1), dtype=torch.int32, device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    nb = a.mask_bytes()
+    tr, tr_b = (torch.zeros((n_steps, nr), dtype=torch.float64, device="cuda") for _ in range(2))
+    mk, mk_b = (torch.full((n_steps, nb), 255, dtype=torch.uint8, device="cuda")
+                for _ in range(2))
+    g = torch.randn((n_steps + 1, nr), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    C.check(L.ws_step_traces(a._ctx, n_steps, dt, 0, nr, p(ij), p(tr), p(mk), nb, last))
+    for s in range(n_steps):
+        b.step_record_masks(dt, mk_b[s])
+        b.gather(0, 0, ij, tr_b[s])
+    torch.cuda.synchronize()
+    assert torch.equal(tr, tr_b)
+    assert torch.equal(mk, mk_b)
+    assert torch.equal(a.state_view(0), b.state_view(0))
+    if last:
+        _same(a, b)
+    lam = [a.new_buffer() for _ in range(4)]
+    for x in (lam[0], lam[2]):
+        a.patch_view(x, 0)[0, 2:-2, 2:-2] = 0.25
+    torch.cuda.synchronize()
+    C.check(L.ws_adjoint_sweep(a._ctx, n_steps, dt, p(mk), nb, 0, nr, p(ij), p(g[1:]), 1, 1,
+                               p(lam[0]), p(lam[1])))
+    b.add_at(0, 0, ij, g[n_steps], buf=lam[2])
+    for s in range(n_steps - 1, -1, -1):
+        b.adjoint_step(dt, mk_b[s], lam[2], lam[3])
+        b.add_at(0, 0, ij, g[s], buf=lam[3])
+        lam[2], lam[3] = lam[3], lam[2]
+    torch.cuda.synchronize()
+    assert torch.equal(a.patch_view(lam[n_steps % 2], 0), b.patch_view(lam[2], 0))
