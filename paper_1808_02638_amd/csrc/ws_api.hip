@@ -56,6 +56,10 @@ bool same_rel(double a, double b) { return std::fabs(a - b) <= 1e-12 * std::fabs
 // Receivers an adjoint step adds itself (one look per lane and 64 of them).
 constexpr int kMaxFusedAdds = 256;
 
+// Cuts per direction of a tiled level that a two-step launch takes (a
+// wavefront holds them one per lane).
+constexpr size_t kMaxDomainCuts = 64;
+
 constexpr int kTileWidths[] = {8, 16, 32, 64, 128, 256};
 
 struct PoolLayout {
@@ -277,6 +281,11 @@ struct ws_ctx {
   std::vector<PackWave> packs;  // wavefronts of the PACKED tiles
   std::vector<TileEntry> two_tiles;  // tiles of the two-step launch (empty: it does not apply)
   int two_rows = 0;                  // rows per segment of theirs
+  // a tiled level cut along full columns and rows: its cuts, and the patch of
+  // each place (empty: cut otherwise)
+  std::vector<int32_t> xcut, ycut, place;
+  int link_periodic = 0;
+  int64_t domain_off = 0;  // workspace offset of the two-step launch's domain table
   std::vector<TileEntry> stiles;  // conservation-sum tiles (fixed by the patch sizes)
   std::vector<int> order;  // patches largest first
   int n_cu = 0, wg_per_cu = 0, grid = 0, occupancy = 0;
@@ -356,6 +365,17 @@ struct ws_ctx {
     a.tiles = d_tiles() + tiles.size();
     a.n_tiles = (int32_t)two_tiles.size();
     a.seg_rows = two_rows;
+    if (!place.empty()) {
+      Domain &d = a.domain;
+      d.patches = reinterpret_cast<const DomainPatch *>(ws + domain_off);
+      d.xcut = reinterpret_cast<const int32_t *>(d.patches + place.size());
+      d.ycut = d.xcut + xcut.size();
+      d.na = (int32_t)xcut.size() - 1;
+      d.nb = (int32_t)ycut.size() - 1;
+      d.mx = xcut.back();
+      d.my = ycut.back();
+      d.periodic = link_periodic;
+    }
   }
 
   void drop_graph() {
@@ -378,9 +398,13 @@ struct ws_ctx {
   void build_two_tiles() {
     two_tiles.clear();
     if (medium || (limiter & WS_TRANSVERSE_CORR)) return;
+    const bool domain = !place.empty();
+    if (link_src && !domain) return;
+    if (domain && P.elems * (dtype == WS_F32 ? 4 : 8) >= (int64_t{1} << 31)) return;
     for (const PatchRow &r : rows)
-      if (r.bc != WS_BC_EXTRAP || !march_fits(r.plane, dtype)) return;
+      if (!domain && (r.bc != WS_BC_EXTRAP || !march_fits(r.plane, dtype))) return;
     auto count = [&](int seg) {
+      if (domain) return ceil_div(xcut.back(), kMultiCols) * ceil_div(ycut.back(), 4 * seg);
       int64_t n = 0;
       for (const PatchRow &r : rows) n += ceil_div(r.mx, kMultiCols) * ceil_div(r.my, 4 * seg);
       return n;
@@ -392,21 +416,54 @@ struct ws_ctx {
     // time per round of them plus half of one for the last round after that.
     // Measured (FP64, us per step): 2048^2 at 26 rows, 740 workgroups on 768
     // places, 20.9; at 20 rows, 962 of them, 22.0; 13 rows 21.7, 8 rows 22.8.
-    const double places = (double)n_cu * std::max(1, step_two_occupancy(dtype, limiter));
+    const double places = (double)n_cu * std::max(1, step_two_occupancy(dtype, limiter, domain));
     double best = 0.0;
     for (int seg = 4; seg <= kMaxTwoRows; ++seg) {
       const double rounds = count(seg) / places;
       const double cost = (seg + 7) * (rounds <= 1.0 ? 0.6 + 0.4 * rounds : rounds + 0.5);
       if (seg == 4 || cost < best) best = cost, two_rows = seg;
     }
-    if ((int64_t)tiles.size() + count(two_rows) > L.max_tiles) return;
-    for (int k : order) {
-      const PatchRow &r = rows[k];
-      const int ntx = (int)ceil_div(r.mx, kMultiCols), nty = (int)ceil_div(r.my, 4 * two_rows);
+    // a tiled level's table: its patches, then its cuts
+    const int64_t n_tab =
+        domain ? ceil_div((int64_t)place.size() * sizeof(DomainPatch) +
+                              4 * (int64_t)(xcut.size() + ycut.size()) + 16,
+                          sizeof(TileEntry))
+               : 0;
+    if ((int64_t)tiles.size() + count(two_rows) + n_tab > L.max_tiles) return;
+    auto add = [&](int k, int mx, int my) {
+      const int ntx = (int)ceil_div(mx, kMultiCols), nty = (int)ceil_div(my, 4 * two_rows);
       for (int ty = 0; ty < nty; ++ty)
         for (int tx = 0; tx < ntx; ++tx)
           two_tiles.push_back(TileEntry{k, (uint16_t)tx, (uint16_t)ty});
+    };
+    if (domain)
+      add(0, xcut.back(), ycut.back());
+    else
+      for (int k : order) add(k, rows[k].mx, rows[k].my);
+    domain_off = L.tiles + round_up((int64_t)(tiles.size() + two_tiles.size()) * sizeof(TileEntry), 16);
+  }
+
+  // Upload the two-step launch's tables (the stream is synchronised after).
+  int upload_two() {
+    if (two_tiles.empty()) return WS_OK;
+    HIPCHK(hipMemcpyAsync(ws + L.tiles + tiles.size() * sizeof(TileEntry), two_tiles.data(),
+                          two_tiles.size() * sizeof(TileEntry), hipMemcpyHostToDevice, stream));
+    if (place.empty()) return WS_OK;
+    const int64_t es = dtype == WS_F32 ? 4 : 8;
+    std::vector<DomainPatch> tab;
+    for (int32_t k : place) {
+      const PatchRow &r = rows[k];
+      tab.push_back(DomainPatch{(uint32_t)((r.q_off + r.col0 - 2) * es), (uint32_t)(r.ld * es),
+                                (uint32_t)(r.plane * es), 0});
     }
+    std::vector<int32_t> cuts(xcut);
+    cuts.insert(cuts.end(), ycut.begin(), ycut.end());
+    const int64_t nt = (int64_t)(tab.size() * sizeof(DomainPatch));
+    HIPCHK(hipMemcpyAsync(ws + domain_off, tab.data(), nt, hipMemcpyHostToDevice, stream));
+    HIPCHK(hipMemcpyAsync(ws + domain_off + nt, cuts.data(), 4 * cuts.size(),
+                          hipMemcpyHostToDevice, stream));
+    HIPCHK(hipStreamSynchronize(stream));  // the tables above are this call's
+    return WS_OK;
   }
 
   // Tile list: patches largest first, each patch's tiles row by row; then the
@@ -435,9 +492,7 @@ struct ws_ctx {
     HIPCHK(hipMemcpyAsync(ws + L.tiles, tiles.data(), tiles.size() * sizeof(TileEntry),
                           hipMemcpyHostToDevice, stream));
     build_two_tiles();
-    if (!two_tiles.empty())
-      HIPCHK(hipMemcpyAsync(ws + L.tiles + tiles.size() * sizeof(TileEntry), two_tiles.data(),
-                            two_tiles.size() * sizeof(TileEntry), hipMemcpyHostToDevice, stream));
+    if (int rc = upload_two()) return rc;
     if (!packs.empty())
       HIPCHK(hipMemcpyAsync(ws + L.packs, packs.data(), packs.size() * sizeof(PackWave),
                             hipMemcpyHostToDevice, stream));
@@ -789,7 +844,29 @@ int ws_link_level(ws_ctx *c, const int32_t *origins, int32_t domain_mx, int32_t 
   c->link_max_ring = 0;
   for (const PatchRow &r : c->rows) c->link_max_ring = std::max(c->link_max_ring, ring_size(r.mx, r.my));
   c->drop_graph();
-  return WS_OK;
+  // whether the patches cut the domain along full columns and rows: the
+  // origins' columns times rows are then all the patches there are
+  c->xcut.clear(), c->ycut.clear(), c->place.clear();
+  c->link_periodic = periodic;
+  std::vector<int32_t> xs, ys;
+  for (int k = 0; k < c->n_patches; ++k) xs.push_back(origins[2 * k]), ys.push_back(origins[2 * k + 1]);
+  for (std::vector<int32_t> *v : {&xs, &ys}) {
+    std::sort(v->begin(), v->end());
+    v->erase(std::unique(v->begin(), v->end()), v->end());
+  }
+  if (xs.size() * ys.size() == (size_t)c->n_patches && 
+      xs.size() < kMaxDomainCuts && ys.size() < kMaxDomainCuts) {
+    c->place.resize(c->n_patches);
+    for (int k = 0; k < c->n_patches; ++k) {
+      const size_t a = std::lower_bound(xs.begin(), xs.end(), origins[2 * k]) - xs.begin();
+      const size_t b2 = std::lower_bound(ys.begin(), ys.end(), origins[2 * k + 1]) - ys.begin();
+      c->place[b2 * xs.size() + a] = k;
+    }
+    c->xcut = xs, c->ycut = ys;
+    c->xcut.push_back(domain_mx), c->ycut.push_back(domain_my);
+  }
+  c->build_two_tiles();
+  return c->upload_two();
 }
 
 int ws_get_tiling(ws_ctx *c, int32_t *variant, int32_t *tile_w, int32_t *tile_h,
@@ -981,10 +1058,12 @@ int ws_capture_steps(ws_ctx *c, int32_t n_steps, double cfl_desired) {
   // n_steps single steps leave it in, and the last step is a single one, so
   // that the other pool holds the state before it and every reported Courant
   // number is that step's.
-  const int pairs = c->two_tiles.empty() || c->link_src ? 0 : (n_steps - 1) / 4 * 2;
+  const int pairs = c->two_tiles.empty() ? 0 : (n_steps - 1) / 4 * 2;
   int src = c->cur;
   for (int s = 0; s < pairs && rc == WS_OK; ++s, src = 1 - src)
     rc = enqueue_two(c, src, cfl_desired);
+  // pairs of steps of a tiled level leave its ghosts to the first single one
+  if (pairs > 0 && rc == WS_OK) rc = link_after_step(c, src);
   for (int s = 2 * pairs; s < n_steps && rc == WS_OK; ++s, src = 1 - src)
     rc = enqueue_auto(c, src, cfl_desired);
   hipGraph_t g = nullptr;

@@ -45,6 +45,7 @@ struct StepArgs {
   uint8_t *masks;        // nullptr unless the branches are recorded
   const void *medium;    // nullptr, or per-cell (c, Z) planes laid out like a q pool
   // two-step launch only
+  Domain domain;         // a tiled level (na > 0): its tiles cut the domain
   int32_t seg_rows;      // rows per segment
   uint8_t *masks2;       // branches of the second step (masks: of the first)
   int32_t rec_patch, rec_n;  // receivers: cells of one patch, FP64 levels only
@@ -63,12 +64,13 @@ constexpr int kMediumFlag = 0x10000;
 hipError_t launch_step(int dtype, int limiter, int vars, const StepArgs &a, int grid,
                        hipStream_t s);
 // Two steps in one launch (ws_multi.hip): homogeneous levels whose patches all
-// have extrapolation boundaries, default transverse variant; a.tiles are
+// have extrapolation boundaries, or tiled ones (a.domain), default transverse
+// variant; a.tiles are
 // kMultiCols columns by 4 seg_rows rows; a.dt_override > 0 fixes dt, else
 // a.cfl_desired > 0 rescales it after each of the two steps.
 hipError_t launch_step_two(int dtype, int limiter, const StepArgs &a, hipStream_t s);
 // Workgroups of that launch a CU holds at once (0: unknown).
-int step_two_occupancy(int dtype, int limiter);
+int step_two_occupancy(int dtype, int limiter, bool domain);
 // The ghost ring of an mx x my patch in one numbering, shared by the kernels
 // that walk it and the host tables indexed by it: rows -2, -1 across the
 // padded width, rows my, my+1, then columns -2, -1, mx, mx+1 of the interior

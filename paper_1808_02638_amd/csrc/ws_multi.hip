@@ -1,5 +1,6 @@
 // Two level steps in one launch (gfx950), for the captured step loop of
-// homogeneous levels whose patches have extrapolation boundaries.
+// homogeneous levels whose patches have extrapolation boundaries, and of tiled
+// levels.
 //
 // The step's rate is set by HBM (or the Infinity Cache): every launch reads
 // and writes the whole state, while its arithmetic takes well under half of
@@ -11,6 +12,9 @@
 // shifts.  A step reaches two columns and two rows to each side, so of the 64
 // lanes the middle 56 are updated (60 with one step), and a segment's first
 // step covers two rows more at each end than its second.
+//
+// A tiled level whose patches cut the domain along full columns and rows is
+// worked as that one domain.
 //
 // Every quantity has the expression the one-step sweeps give it
 // (march_up, cell_update), so a cell's result is bitwise that of two steps.
@@ -103,6 +107,22 @@ __device__ inline float lane_value(float v, int from) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), from));
 }
 
+// The lanes on ghost columns (glo, ghi: of the low, the high side) take the
+// new value of the nearest column, on lane lo or hi, through scalar registers:
+// two lane reads per value and side.  lo <= 0 or hi >= 63: no such lanes.
+template <typename T>
+__device__ inline void nearest_columns(Row3<T> &N, int lo, int hi, bool glo, bool ghi) {
+  if (lo > 0) {
+    const T p = lane_value(N.p, lo), u = lane_value(N.u, lo), v = lane_value(N.v, lo);
+    if (glo) N.p = p, N.u = u, N.v = v;
+  }
+  if (hi < kMarchWidth - 1) {
+    const int from = max(hi, 0);
+    const T p = lane_value(N.p, from), u = lane_value(N.u, from), v = lane_value(N.v, from);
+    if (ghi) N.p = p, N.u = u, N.v = v;
+  }
+}
+
 // Lanes of one segment: lane l holds column i of the patch, lanes kMultiHalo
 // .. 63 - kMultiHalo are updated.  Reads take the nearest interior cell (the
 // extrapolation ghosts).  Rows are addressed by a scalar offset that is
@@ -153,8 +173,14 @@ struct MultiLanes {
     if (own || edge) row[0] = (uint8_t)(own ? branches : branches & 15u);
     if (r == my - 1 && (own || edge)) row[mx + 1] = (uint8_t)(own ? top : 0u);  // no edge owns the corner
   }
+  // Rows outside the patch copy its first and last row.
+  __device__ bool clamp_y() const { return true; }
   // Whether the segment holds ghost columns.
   __device__ bool ghosts() const { return lo > 0 || hi < kMarchWidth - 1; }
+  // A place in the rows read or stored, stepped up row by row.
+  struct Cursor {
+    unsigned o;
+  };
   __device__ unsigned row_offset(int r) const {
     return (unsigned)(min(max(r, 0), rmax) + 2) * ldb;
   }
@@ -164,24 +190,143 @@ struct MultiLanes {
     S.v = bload<T>(ib, colb, o + 2 * plb);
   }
   __device__ void fetch(Row3<T> &S, int r) const { fetch_at(S, row_offset(r)); }
-  // The lanes on ghost columns take the new value of the nearest column
-  // (through scalar registers: two lane reads per value and side).
+  __device__ Cursor read_from(int r) const { return Cursor{row_offset(r)}; }
+  __device__ void fetch_next(Row3<T> &S, Cursor &c) const {
+    fetch_at(S, c.o);
+    c.o = min(c.o + ldb, row_offset(rmax));
+  }
+  __device__ Cursor store_from(int r) const { return Cursor{(unsigned)(r + 2) * ldb}; }
+  // Row r, with its ghost rows (EDGE).
+  template <bool EDGE>
+  __device__ void store_next(const Row3<T> &N, Cursor &c, int r) const {
+    if constexpr (EDGE) {
+      if (r == 0) put_at(N, 0), put_at(N, ldb);
+      if (r == my - 1) put_at(N, c.o + ldb), put_at(N, c.o + 2 * ldb);
+    }
+    put_at(N, c.o);
+    c.o += ldb;
+  }
   __device__ void ghost_columns(Row3<T> &N) const {
-    if (lo > 0) {
-      const T p = lane_value(N.p, lo), u = lane_value(N.u, lo), v = lane_value(N.v, lo);
-      if (glo) N.p = p, N.u = u, N.v = v;
-    }
-    if (hi < kMarchWidth - 1) {
-      const int from = max(hi, 0);
-      const T p = lane_value(N.p, from), u = lane_value(N.u, from), v = lane_value(N.v, from);
-      if (ghi) N.p = p, N.u = u, N.v = v;
-    }
+    nearest_columns(N, lo, hi, glo, ghi);
   }
   __device__ void put_at(const Row3<T> &N, unsigned o) const {
     bstore(ob, N.p, ocolb, o);
     bstore(ob, N.u, ocolb, o + plb);
     bstore(ob, N.v, ocolb, o + 2 * plb);
   }
+};
+
+// Lanes of one segment of a tiled level, whose patches cut one domain along
+// full columns and rows: lane l holds column i of the domain, wherever the
+// patches' edges fall, and the march crosses from a patch to the one above it.
+// So the segment reads what the ghosts stand for, and no ghosts are needed
+// between the launches.  A lane keeps its patch's addressing (the patches of a
+// wavefront may have different strides) and takes the next patch's from the
+// table when the march leaves a row of patches.  Outside the domain, columns
+// and rows wrap around or copy the nearest one.  Pools under 2^31 bytes.
+template <typename T>
+struct DomainLanes {
+  __amdgpu_buffer_rsrc_t ib, ob;  // the two pools
+  const DomainPatch *tab;         // row of patches by row of patches
+  int ycut;                       // lane b: where row b of patches starts (b = nb: the end)
+  int na, nb, my, rmax, r0, r1;   // patches per row, rows of patches; the domain's rows
+  bool wrap;                      // rows wrap around
+  int a;                          // the lane's column of patches
+  unsigned colb;                  // its offset in a row of its patch
+  int lo, hi;                     // lanes of columns 0 and mx-1 (clamped columns only)
+  bool glo, ghi, own;
+
+  struct Cursor {
+    unsigned o, ldb, plb;  // the lane's place, row and plane strides (bytes)
+    int row, end, b;       // row of the domain, end of the row of patches, its index
+  };
+
+  __device__ DomainLanes(const StepArgs &A, int i0, int l, int r0_, int r1_) {
+    constexpr int halo = kMultiHalo;
+    ib = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(A.qin), 0, A.pool_bytes,
+                                           kRawBufferWord3);
+    ob = __builtin_amdgcn_make_buffer_rsrc(A.qout, 0, A.pool_bytes, kRawBufferWord3);
+    const Domain &D = A.domain;
+    tab = D.patches;
+    na = D.na;
+    nb = D.nb;
+    ycut = D.ycut[min(l, nb)];
+    const int xcut = D.xcut[min(l, na)];
+    my = D.my;
+    wrap = (D.periodic & 2) != 0;
+    r0 = r0_;
+    r1 = r1_;
+    rmax = r1 + 3;
+    const int i = i0 + l, mx = D.mx;
+    own = l >= halo && l < kMarchWidth - halo && i < mx;
+    const bool wrap_x = (D.periodic & 1) != 0;
+    lo = wrap_x ? 0 : -i0;
+    hi = wrap_x ? kMarchWidth : mx - 1 - i0;
+    glo = !wrap_x && i < 0;
+    ghi = !wrap_x && i >= mx;
+    const int c = wrap_x ? (i % mx + mx) % mx : min(max(i, 0), mx - 1);
+    a = 0;
+    int x0 = 0;
+    for (int n = 1; n < na; ++n) {
+      const int x = __builtin_amdgcn_readlane(xcut, n);
+      if (c >= x) a = n, x0 = x;
+    }
+    colb = (unsigned)(c - x0 + 2) * (unsigned)sizeof(T);
+  }
+  __device__ bool clamp_y() const { return !wrap; }
+  __device__ bool ghosts() const { return lo > 0 || hi < kMarchWidth - 1; }
+  __device__ Cursor cursor(int r, bool store) const {
+    Cursor c;
+    c.row = wrap ? (r % my + my) % my : min(max(r, 0), my - 1);
+    c.b = 0;
+    while (c.b + 1 < nb && c.row >= __builtin_amdgcn_readlane(ycut, c.b + 1)) ++c.b;
+    place(c, store);
+    return c;
+  }
+  // The lane's addressing in the cursor's row of patches.
+  __device__ void place(Cursor &c, bool store) const {
+    const DomainPatch p = tab[c.b * na + a];
+    const int y0 = __builtin_amdgcn_readlane(ycut, c.b);
+    c.end = __builtin_amdgcn_readlane(ycut, c.b + 1);
+    c.ldb = p.ldb;
+    c.plb = p.plb;
+    c.o = p.off + (unsigned)(c.row - y0 + 2) * p.ldb + colb;
+    if (store && !own) c.o = kDropOffset, c.ldb = 0, c.plb = 0;
+  }
+  __device__ void step(Cursor &c, bool store) const {
+    if (c.row + 1 < c.end) {
+      c.row += 1;
+      c.o += c.ldb;
+      return;
+    }
+    if (c.b + 1 == nb && !wrap) return;  // the last row stands for those above it
+    c.b = c.b + 1 == nb ? 0 : c.b + 1;
+    c.row = __builtin_amdgcn_readlane(ycut, c.b);
+    place(c, store);
+  }
+  __device__ void load(Row3<T> &S, const Cursor &c) const {
+    S.p = bload<T>(ib, c.o, 0);
+    S.u = bload<T>(ib, c.o + c.plb, 0);
+    S.v = bload<T>(ib, c.o + 2 * c.plb, 0);
+  }
+  __device__ void fetch(Row3<T> &S, int r) const { load(S, cursor(r, false)); }
+  __device__ Cursor read_from(int r) const { return cursor(min(r, rmax), false); }
+  __device__ void fetch_next(Row3<T> &S, Cursor &c) const {
+    load(S, c);
+    step(c, false);
+  }
+  __device__ Cursor store_from(int r) const { return cursor(r, true); }
+  template <bool EDGE>
+  __device__ void store_next(const Row3<T> &N, Cursor &c, int) const {
+    bstore(ob, N.p, c.o);
+    bstore(ob, N.u, c.o + c.plb);
+    bstore(ob, N.v, c.o + 2 * c.plb);
+    step(c, true);
+  }
+  __device__ void ghost_columns(Row3<T> &N) const {
+    nearest_columns(N, lo, hi, glo, ghi);
+  }
+  __device__ void record(uint8_t *, int, unsigned, unsigned) const {}
 };
 
 // Rows [r0, r1) advanced by two steps.  Set j holds row r0-2+j of the input
@@ -192,14 +337,15 @@ struct MultiLanes {
 // its row 0 and those above it of its last row.  The other segments' loop has
 // no branches: a wavefront alone on its SIMD issues one instruction of any
 // kind per four cycles, so what goes into branches and addresses counts.
-template <typename T, int LIM, bool EDGE, bool MASKS>
-__device__ __attribute__((always_inline)) inline void march_two(const MultiLanes<T> &M,
+template <typename T, int LIM, bool EDGE, bool MASKS, class L>
+__device__ __attribute__((always_inline)) inline void march_two(const L &M,
                                                                 const Coef<T> &ka,
                                                                 const Coef<T> &kb,
                                                                 uint8_t *masks,
                                                                 uint8_t *masks2) {
   const int r0 = M.r0, r1 = M.r1;
-  const bool bottom = EDGE && r0 == 0;
+  const bool clamp = EDGE && M.clamp_y();  // (without: the rows wrap around)
+  const bool bottom = clamp && r0 == 0;
   Row3<T> R[kMultiSets], W[3], M2, M1, e0, e1;
   const int q0 = bottom ? 0 : r0 - 2;  // first row of the first step
   M.fetch(M2, q0 - 2);
@@ -231,12 +377,11 @@ __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes
   W[0] = first(R[2], R[3], R[4], r0);
   if (bottom) e0 = W[0], e1 = W[0];
   W[1] = first(R[3], R[4], R[5], r0 + 1);
-  if (EDGE && r0 + 1 >= M.my) W[1] = W[0];
+  if (clamp && r0 + 1 >= M.my) W[1] = W[0];
   S2 = carry_in<T, LIM, MASKS>(kb, e0, e1, W[0], W[1]);
 
-  // offsets of the row stored and of the row fetched next
-  unsigned oo = (unsigned)(r0 + 2) * M.ldb, oi = M.row_offset(r0 + 8);
-  const unsigned omax = M.row_offset(M.rmax);
+  // the row fetched next and the row stored
+  typename L::Cursor in = M.read_from(r0 + 8), out = M.store_from(r0);
   auto row = [&](Row3<T> &A, const Row3<T> &B, const Row3<T> &C, const Row3<T> &Wa,
                  const Row3<T> &Wb, Row3<T> &Wc, int r) {
     __builtin_amdgcn_sched_barrier(0);
@@ -245,7 +390,7 @@ __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes
     if constexpr (MASKS) M.record(masks, r + 2, br, S.ybits);
     if constexpr (EDGE) {
       M.ghost_columns(Wc);
-      if (r + 2 >= M.my) {
+      if (clamp && r + 2 >= M.my) {
         asm volatile("");  // a branch taken on two rows, not selects on each
         Wc = Wb;
       }
@@ -253,16 +398,10 @@ __device__ __attribute__((always_inline)) inline void march_two(const MultiLanes
     __builtin_amdgcn_sched_barrier(0);
     Row3<T> N = row_step<T, LIM, MASKS>(kb, S2, Wa, Wb, Wc, br);
     if constexpr (MASKS) M.record(masks2, r, br, S2.ybits);
-    if constexpr (EDGE) {
-      M.ghost_columns(N);
-      if (r == 0) M.put_at(N, 0), M.put_at(N, M.ldb);
-      if (r == M.my - 1) M.put_at(N, oo + M.ldb), M.put_at(N, oo + 2 * M.ldb);
-    }
-    M.put_at(N, oo);
-    oo += M.ldb;
+    if constexpr (EDGE) M.ghost_columns(N);
+    M.template store_next<EDGE>(N, out, r);
     __builtin_amdgcn_sched_barrier(0);
-    M.fetch_at(A, oi);
-    oi = min(oi + M.ldb, omax);
+    M.fetch_next(A, in);
   };
   for (int r = r0;;) {
     row(R[4], R[5], R[0], W[0], W[1], W[2], r);
@@ -325,14 +464,16 @@ __device__ inline void gather_receivers(const StepArgs &a, int first) {
 // overlap.  The last workgroup files the two steps' Courant numbers.
 // Wavefronts per SIMD the registers are kept for: three (153 registers in
 // FP64; four spilled and ran 4x slower), two where branches are recorded
-// (197).
-template <typename T, int LIM, bool MASKS>
+// (197) and on a tiled level, whose lanes carry their own addressing (three
+// spilled 66).
+template <typename T, int LIM, bool MASKS, bool DOMAIN>
 constexpr int two_waves() {
-  return sizeof(T) == 8 && MASKS ? 2 : 3;
+  return sizeof(T) == 8 && (MASKS || DOMAIN) ? 2 : 3;
 }
 
-template <typename T, int LIM, bool MASKS>
-__global__ __launch_bounds__(kThreads, (two_waves<T, LIM, MASKS>())) void step_kernel_two(StepArgs a) {
+// DOMAIN: a tiled level, worked as the one domain its patches cut.
+template <typename T, int LIM, bool MASKS, bool DOMAIN>
+__global__ __launch_bounds__(kThreads, (two_waves<T, LIM, MASKS, DOMAIN>())) void step_kernel_two(StepArgs a) {
   const int work = (a.n_tiles + kGroups - 1) / kGroups * kGroups;  // workgroups of the tiles
   if ((int)blockIdx.x >= work) {
     if ((int)blockIdx.x > work) {
@@ -359,7 +500,8 @@ __global__ __launch_bounds__(kThreads, (two_waves<T, LIM, MASKS>())) void step_k
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const TileEntry te = uniform_row(a.tiles[t]);
   const PatchRow pr = uniform_row(a.patches[te.patch]);
-  const int r0 = (te.ty * 4 + wave) * a.seg_rows, r1 = min(r0 + a.seg_rows, pr.my);
+  const int rows = DOMAIN ? a.domain.my : pr.my;
+  const int r0 = (te.ty * 4 + wave) * a.seg_rows, r1 = min(r0 + a.seg_rows, rows);
   if (r0 >= r1) return;
   const InstRow in = uniform_row(a.inst[pr.inst]);
   const InstMin m = uniform_row(a.slots.inst_min[pr.inst]);
@@ -368,6 +510,14 @@ __global__ __launch_bounds__(kThreads, (two_waves<T, LIM, MASKS>())) void step_k
   const double dt1 = next_dt(dt0, in.c, m, a.cfl_desired, cfl);
   const Coef<T> ka = make_coef<T, LIM>(in.c, in.Z, dt0, pr.dx, pr.dy);
   const Coef<T> kb = make_coef<T, LIM>(in.c, in.Z, dt1, pr.dx, pr.dy);
+  if constexpr (DOMAIN) {
+    const DomainLanes<T> M(a, te.tx * kMultiCols - kMultiHalo, (int)threadIdx.x & 63, r0, r1);
+    if (M.ghosts() || (M.clamp_y() && (r0 == 0 || r1 + 2 > rows)))
+      march_two<T, LIM, true, false>(M, ka, kb, nullptr, nullptr);
+    else
+      march_two<T, LIM, false, false>(M, ka, kb, nullptr, nullptr);
+    return;
+  }
   const int64_t org = pr.q_off + 2 * (int64_t)pr.ld + pr.col0;
   const MultiLanes<T> M(reinterpret_cast<const T *>(a.qin) + org,
                         reinterpret_cast<T *>(a.qout) + org, pr,
@@ -388,12 +538,16 @@ hipError_t two_l(const StepArgs &a, hipStream_t s) {
                              (a.rec_n + kThreads - 1) / kThreads));
   if constexpr (sizeof(T) == 8 && LIM == WS_LIM_MC) {
     if (a.masks) {
-      hipLaunchKernelGGL((step_kernel_two<T, LIM, true>), grid, dim3(kThreads), 0, s, a);
+      if (a.domain.na > 0) return hipErrorInvalidValue;
+      hipLaunchKernelGGL((step_kernel_two<T, LIM, true, false>), grid, dim3(kThreads), 0, s, a);
       return hipGetLastError();
     }
   }
   if (a.masks) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((step_kernel_two<T, LIM, false>), grid, dim3(kThreads), 0, s, a);
+  if (a.domain.na > 0)
+    hipLaunchKernelGGL((step_kernel_two<T, LIM, false, true>), grid, dim3(kThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL((step_kernel_two<T, LIM, false, false>), grid, dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
@@ -415,24 +569,26 @@ hipError_t launch_step_two(int dtype, int limiter, const StepArgs &a, hipStream_
 }
 
 template <typename T, int LIM>
-static int two_occupancy_of() {
+static int two_occupancy_of(bool domain) {
   int n = 0;
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, step_kernel_two<T, LIM, false>,
-                                                      kThreads, 0) ==
-                 hipSuccess
-             ? n
-             : 0;
+  const hipError_t e =
+      domain ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                   &n, step_kernel_two<T, LIM, false, true>, kThreads, 0)
+             : hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                   &n, step_kernel_two<T, LIM, false, false>, kThreads, 0);
+  return e == hipSuccess ? n : 0;
 }
 
 template <typename T>
-static int two_occupancy_t(int limiter) {
-  return limiter == WS_LIM_NONE      ? two_occupancy_of<T, WS_LIM_NONE>()
-         : limiter == WS_LIM_VANLEER ? two_occupancy_of<T, WS_LIM_VANLEER>()
-                                     : two_occupancy_of<T, WS_LIM_MC>();
+static int two_occupancy_t(int limiter, bool domain) {
+  return limiter == WS_LIM_NONE      ? two_occupancy_of<T, WS_LIM_NONE>(domain)
+         : limiter == WS_LIM_VANLEER ? two_occupancy_of<T, WS_LIM_VANLEER>(domain)
+                                     : two_occupancy_of<T, WS_LIM_MC>(domain);
 }
 
-int step_two_occupancy(int dtype, int limiter) {
-  return dtype == WS_F32 ? two_occupancy_t<float>(limiter) : two_occupancy_t<double>(limiter);
+int step_two_occupancy(int dtype, int limiter, bool domain) {
+  return dtype == WS_F32 ? two_occupancy_t<float>(limiter, domain)
+                         : two_occupancy_t<double>(limiter, domain);
 }
 
 }  // namespace ws

@@ -74,6 +74,21 @@ struct InstRow {
   double c, Z;
 };
 
+// One patch of a tiled level, for the two-step launch: pool byte offset of its
+// padded cell (-2, -2) of plane p, row and plane strides (bytes).
+struct DomainPatch {
+  uint32_t off, ldb, plb, pad_;
+};
+
+// A tiled level whose patches cut the domain along full columns and rows:
+// patch (a, b) holds columns [xcut[a], xcut[a+1]) and rows [ycut[b], ycut[b+1])
+// and is row b * na + a of the table.  na = 0: none.
+struct Domain {
+  const DomainPatch *patches;
+  const int32_t *xcut, *ycut;
+  int32_t na, nb, mx, my, periodic;  // periodic: bit 0 x, bit 1 y
+};
+
 // Workspace carve-up (byte offsets inside the caller's workspace buffer).
 struct WsLayout {
   int64_t patches, inst, tiles, packs, stiles, dt, cfl_tile, inst_acc, cfl_last, cfl_max,

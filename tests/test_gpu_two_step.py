@@ -78,6 +78,37 @@ def test_every_remainder_of_the_pairing(ws, n):
     _same(a, b)
 
 
+@pytest.mark.parametrize("dtype,limiter", [(torch.float64, "mc"), (torch.float64, "vanleer"),
+                                           (torch.float32, "mc")])
+@pytest.mark.parametrize("xs,ys", [([0, 3], [0, 2]), ([0, 1, 2, 5], [0, 1, 4, 5]),
+                                   ([0, 57, 61, 130], [0, 2, 40, 77]), ([0, 200, 300], [0, 211])])
+@pytest.mark.parametrize("periodic", [(False, False), (True, False), (False, True), (True, True)])
+def test_tiled_pairs_equal_single_steps(ws, xs, ys, periodic, dtype, limiter):
+    """A tiled level's pairs of steps work the domain as a whole; ghosts too."""
+    g = torch.Generator().manual_seed(5)
+    size = [(x1 - x0, y1 - y0) for y0, y1 in zip(ys, ys[1:]) for x0, x1 in zip(xs, xs[1:])]
+    org = [(x, y) for y in ys[:-1] for x in xs[:-1]]
+    dx, dy = 1 / xs[-1], 1.3 / ys[-1]
+    q = [torch.randn((3, h + 4, w + 4), generator=g, dtype=torch.float64) for w, h in size]
+    levels = []
+    for _ in range(2):
+        lev = ws.Level([dict(mx=w, my=h, dx=dx, dy=dy) for w, h in size], [(1.0, 4.0)],
+                       dtype=dtype, limiter=limiter)
+        lev.link(org, (xs[-1], ys[-1]), periodic=periodic)
+        for k in range(lev.n):
+            lev.upload(k, q[k])
+        lev.fill_ghosts()
+        lev.set_dt([0.4 * min(dx, dy)])
+        levels.append(lev)
+    a, b = levels
+    a.capture(6, 0.9)
+    for _ in range(2):
+        a.graph_launch()
+        for _ in range(6):
+            b.step_auto(0.9)
+        _same(a, b)
+
+
 @pytest.mark.parametrize("n_steps,last", [(1, 0), (2, 0), (2, 1), (5, 0), (6, 1)])
 @pytest.mark.parametrize("shape,nr", [((61, 9), 7), ((130, 77), 70), ((57, 40), 300)])
 def test_traces_branches_and_sweep(ws, shape, nr, n_steps, last):
