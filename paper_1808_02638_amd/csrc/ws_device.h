@@ -128,6 +128,22 @@ __device__ inline double max_zero(double a) {
   asm("v_max_f64 %0, %1, 0" : "=v"(r) : "v"(a));
   return r;
 }
+// x / s where x = ab > 0 neither over- nor underflowed and s = a + b (the only
+// quotients kept), so s lies well inside the type's range and none of the
+// scaling of a general division is needed: the hardware reciprocal, refined
+// once in FP64 by Newton's iteration, then the quotient corrected by its
+// residual, which leaves it within 0.5 ulp + 2^-40 of it.  6 instructions in
+// FP64 and 4 in FP32 instead of 11 and 10.
+__device__ inline double quotient(double x, double s) {
+  double r = __builtin_amdgcn_rcp(s);
+  r = fma(r, fma(-s, r, 1.0), r);
+  const double q = x * r;
+  return fma(fma(-q, s, x), r, q);
+}
+__device__ inline float quotient(float x, float s) {
+  const float r = __builtin_amdgcn_rcpf(s), q = x * r;
+  return fmaf(fmaf(-q, s, x), r, q);
+}
 template <typename T, int LIM>
 __device__ inline T limited(T a, T b) {
   if constexpr (LIM == WS_LIM_NONE) {
@@ -136,7 +152,7 @@ __device__ inline T limited(T a, T b) {
     // van Leer, phi(theta) = (theta + |theta|)/(1 + |theta|) with theta = b/a:
     // 0 unless a and b share a sign, then 2ab/(a + b)
     // (the quotient is formed either way: a select costs less than a branch)
-    const T ab = a * b, r = ab / (a + b);
+    const T ab = a * b, r = quotient(ab, a + b);
     return ab > T(0) ? r : T(0);
   } else if constexpr (sizeof(T) == 4) {
     const float t = __builtin_amdgcn_fmed3f(0.0f, a, b);
