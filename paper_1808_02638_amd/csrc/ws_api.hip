@@ -60,6 +60,13 @@ constexpr int kMaxFusedAdds = 256;
 // wavefront holds them one per lane).
 constexpr size_t kMaxDomainCuts = 64;
 
+// Default rows of a MARCH segment on a level that fills the GPU.
+constexpr int kMarchCap = 12;
+// Workgroups per CU by default: more than fit at once, so that the dispatcher
+// hands out the tiles (a workgroup each up to 8192 of them on 256 CUs).  The
+// finest benchmark level: 48 us per step with 32, 58 with the four that fit.
+constexpr int kDefaultWgPerCu = 32;
+
 constexpr int kTileWidths[] = {8, 16, 32, 64, 128, 256};
 
 struct PoolLayout {
@@ -176,21 +183,24 @@ bool valid_tile(int variant, int tw, int th) {
   return th >= nty && th % nty == 0 && th / nty <= rmax;
 }
 
-// Default tiling.  Patches at least 24 cells wide (not periodic): MARCH tiles
-// of four 60-column segments.  A large patch gets the segment height that
-// makes its tile count just fit one round of resident workgroups (assumed 4
-// per CU); a small one spreads its rows over the four segments (up to 16
-// rows each, so that many patches fill the GPU together); up to 64 rows per
-// segment.  Narrower patches: DIRECT tiles whose width in {8..64} wastes the
-// fewest columns (larger on ties), up to 8 rows per thread.
-void default_tile(int mx, int my, int bc, int n_cu, int *variant, int *tw, int *th) {
-  if (mx >= 24 && bc != WS_BC_PERIODIC) {
+// Rows of a MARCH tile whose segments have at most `cap` rows: as many tiles
+// up the patch as that takes, their rows spread evenly.
+int march_rows(int my, int cap) {
+  const int n = (my + 4 * cap - 1) / (4 * cap);
+  return 4 * ((my + 4 * n - 1) / (4 * n));
+}
+
+// Default tiling.  Patches at least 16 cells wide (not periodic): MARCH tiles
+// (a level that mixes in DIRECT tiles runs a kernel with the registers of
+// both; the finest benchmark level, 2784 patches of 16 to 64 cells, ran
+// 58 us with its narrow patches DIRECT and 48 without); their height is the
+// level's affair (segment_rows).  Narrower patches: DIRECT tiles whose width in
+// {8..64} wastes the fewest columns (larger on ties), up to 8 rows per thread.
+void default_tile(int mx, int my, int bc, int *variant, int *tw, int *th) {
+  if (mx >= 16 && bc != WS_BC_PERIODIC) {
     *variant = kMarch;
     *tw = kMarchWidth;
-    const int ntx = (mx + kMarchWidth - 5) / (kMarchWidth - 4);
-    const int tile_rows = std::max(1, 4 * std::max(n_cu, 1) / ntx);  // rows of tiles
-    const int seg = (my + 4 * tile_rows - 1) / (4 * tile_rows);      // rows per segment
-    *th = 4 * std::max(std::min(seg, kMaxMarchRows), std::min(16, (my + 3) / 4));
+    *th = march_rows(my, kMarchCap);
     return;
   }
   *variant = kDirect;
@@ -212,30 +222,29 @@ void default_tile(int mx, int my, int bc, int n_cu, int *variant, int *tw, int *
   *th = nty * r;
 }
 
-// A level whose default tiles leave much of the GPU idle is bound by one
-// segment's march, so its MARCH segments get shorter: 8 or 4 rows while the
-// workgroups stay within a round and a quarter of the places (four per CU),
-// 2 or 1 only while a sixteenth of the places is taken (a segment loads ten
-// rows whatever its height).  Steps of one FP64 patch back to back, us: 64^2
-// 9.3 with 16 rows, 5.2 with 4, 4.3 with 1; 201 x 147 16.4, 5.3 and 6.4;
-// 512^2 9.6 with 16, 7.0 with 8, 6.5 with 4, 7.3 with 2, 9.3 with 1; 1024^2
-// 14.0 with 16, 12.6 with 8, 12.0 with 4, 16.3 with 2.  Only powers of two:
-// heights between them measured slower than both.
-void short_segments(std::vector<PatchRow> &rows, int n_cu) {
-  auto count = [&](int seg) {
+// Rows per MARCH segment of a level with default tiles: 12 where that gives
+// more than a round and a quarter of workgroups (four per CU), else 6 where
+// that gives half a round, else 4; 2 or 1 while a sixteenth of the places is
+// taken (a segment loads ten rows whatever its height).  Not 8 or 16: their
+// last loop refills six rows that no row reads.  One FP64 step, us: 4096^2 201
+// with 12 rows, 203 with 6, 229 with 16, 236 with 64; 2048^2 33.4 with 12, 34.7
+// with 6, 36.4 with 16; 1024^2 12.5 with 4, 13.0 with 6, 15.4 with 12; 512^2
+// 6.5 with 4, 7.3 with 2; 64^2 4.3 with 1, 5.2 with 4, 9.3 with 16; 2784
+// patches of 16 to 64 cells a side 48.1 with 12, 49.1 with 6, 50.7 with 16.
+void segment_rows(std::vector<PatchRow> &rows, int n_cu) {
+  auto count = [&](int cap) {
     int64_t n = 0;
-    for (const PatchRow &r : rows) {
-      const int th = r.variant == kMarch ? std::min(r.th, 4 * seg) : r.th;
-      n += tiles_of(r.mx, r.my, r.variant, r.tw, th);
-    }
+    for (const PatchRow &r : rows)
+      n += tiles_of(r.mx, r.my, r.variant, r.tw, r.variant == kMarch ? march_rows(r.my, cap) : r.th);
     return n;
   };
   const int64_t places = 4 * (int64_t)std::max(n_cu, 1);
-  int seg = 16;
-  while (seg > 1 && count(seg / 2) <= (seg > 4 ? places + places / 4 : places / 16)) seg /= 2;
-  if (seg == 16) return;
+  int cap = kMarchCap;
+  if (count(cap) < places + places / 4) cap = 6;
+  if (cap == 6 && count(cap) < places / 2) cap = 4;
+  while (cap <= 4 && cap > 1 && count(cap / 2) <= places / 16) cap /= 2;
   for (PatchRow &r : rows)
-    if (r.variant == kMarch) r.th = std::min(r.th, 4 * seg);
+    if (r.variant == kMarch) r.th = march_rows(r.my, cap);
 }
 
 // MARCH tiles address a patch with 32-bit byte offsets (all three planes).
@@ -290,7 +299,7 @@ struct ws_ctx {
   std::vector<int> order;  // patches largest first
   int n_cu = 0, wg_per_cu = 0, grid = 0, occupancy = 0;
   int vars = 1;          // tile variants present (bit 0 DIRECT, bit 1 MARCH, bit 2 PACKED)
-  int wg_override = 0;   // workgroups per CU set by the caller (0: occupancy)
+  int wg_override = kDefaultWgPerCu;  // workgroups per CU (set by the caller; 0: occupancy)
   int max_padded_cells = 0;
   int max_ring = 0;  // interior cells next to a side, largest patch
   int max_mx = 0, max_my = 0;
@@ -590,9 +599,9 @@ static int setup_level(ws_ctx *c, const ws_patch_desc *patches, int32_t n_patche
     r.plane = c->P.plane[k];
     r.inst = d.instance;
     r.bc = d.bc;
-    default_tile(d.mx, d.my, d.bc, c->n_cu, &r.variant, &r.tw, &r.th);
+    default_tile(d.mx, d.my, d.bc, &r.variant, &r.tw, &r.th);
     if (r.variant == kMarch && !march_fits(r.plane, dtype)) {
-      default_tile(d.mx, d.my, WS_BC_PERIODIC, c->n_cu, &r.variant, &r.tw, &r.th);  // DIRECT
+      default_tile(d.mx, d.my, WS_BC_PERIODIC, &r.variant, &r.tw, &r.th);  // DIRECT
     }
     r.dx = d.dx;
     r.dy = d.dy;
@@ -603,7 +612,7 @@ static int setup_level(ws_ctx *c, const ws_patch_desc *patches, int32_t n_patche
     c->max_mx = std::max(c->max_mx, d.mx);
     c->max_my = std::max(c->max_my, d.my);
   }
-  short_segments(c->rows, c->n_cu);
+  segment_rows(c->rows, c->n_cu);
   c->mask_total = mask_off;
   sum_tiles(c->rows, c->stiles);
   c->order.resize(n_patches);
@@ -727,8 +736,9 @@ int ws_attach_medium(ws_ctx *c, void *medium, int64_t bytes) {
   for (int k = 0; k < c->n_patches; ++k) {
     PatchRow &r = c->rows[k];
     const bool march = r.mx >= kMarchWidth - 4 && march_fits(r.plane, c->dtype);
-    default_tile(r.mx, r.my, march ? r.bc : WS_BC_PERIODIC, c->n_cu, &r.variant, &r.tw, &r.th);
+    default_tile(r.mx, r.my, march ? r.bc : WS_BC_PERIODIC, &r.variant, &r.tw, &r.th);
   }
+  segment_rows(c->rows, c->n_cu);
   c->drop_graph();
   return c->build_tiles();
 }
