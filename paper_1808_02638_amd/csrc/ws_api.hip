@@ -190,14 +190,15 @@ int march_rows(int my, int cap) {
   return 4 * ((my + 4 * n - 1) / (4 * n));
 }
 
-// Default tiling.  Patches at least 16 cells wide (not periodic): MARCH tiles
-// (a level that mixes in DIRECT tiles runs a kernel with the registers of
-// both; the finest benchmark level, 2784 patches of 16 to 64 cells, ran
-// 58 us with its narrow patches DIRECT and 48 without); their height is the
-// level's affair (segment_rows).  Narrower patches: DIRECT tiles whose width in
-// {8..64} wastes the fewest columns (larger on ties), up to 8 rows per thread.
-void default_tile(int mx, int my, int bc, int *variant, int *tw, int *th) {
-  if (mx >= 16 && bc != WS_BC_PERIODIC) {
+// Width from which a patch takes MARCH tiles whatever else the level holds.
+constexpr int kMarchWide = 16;
+
+// Default tiling.  Patches at least `wide` cells wide (not periodic): MARCH
+// tiles; their height is the level's affair (segment_rows).  Narrower patches:
+// DIRECT tiles whose width in {8..64} wastes the fewest columns (larger on
+// ties), up to 8 rows per thread.
+void default_tile(int mx, int my, int bc, int wide, int *variant, int *tw, int *th) {
+  if (mx >= wide && bc != WS_BC_PERIODIC) {
     *variant = kMarch;
     *tw = kMarchWidth;
     *th = march_rows(my, kMarchCap);
@@ -588,6 +589,17 @@ static int setup_level(ws_ctx *c, const ws_patch_desc *patches, int32_t n_patche
   }
   c->rows.resize(n_patches);
   int64_t mask_off = 0;
+  // A level that mixes in DIRECT tiles runs a kernel with the registers of
+  // both kinds, so narrow patches that hold under a quarter of the cells take
+  // MARCH tiles with the rest (2784 patches, a few of them under 16 cells wide
+  // and the others up to 64: 59 us per step with those DIRECT, 48 without).
+  int64_t cells = 0, narrow = 0;
+  for (int k = 0; k < n_patches; ++k) {
+    const int64_t n = (int64_t)patches[k].mx * patches[k].my;
+    cells += n;
+    if (patches[k].mx < kMarchWide) narrow += n;
+  }
+  const int wide = 4 * narrow < cells ? 1 : kMarchWide;
   for (int k = 0; k < n_patches; ++k) {
     PatchRow &r = c->rows[k];
     const ws_patch_desc &d = patches[k];
@@ -599,9 +611,9 @@ static int setup_level(ws_ctx *c, const ws_patch_desc *patches, int32_t n_patche
     r.plane = c->P.plane[k];
     r.inst = d.instance;
     r.bc = d.bc;
-    default_tile(d.mx, d.my, d.bc, &r.variant, &r.tw, &r.th);
+    default_tile(d.mx, d.my, d.bc, wide, &r.variant, &r.tw, &r.th);
     if (r.variant == kMarch && !march_fits(r.plane, dtype)) {
-      default_tile(d.mx, d.my, WS_BC_PERIODIC, &r.variant, &r.tw, &r.th);  // DIRECT
+      default_tile(d.mx, d.my, WS_BC_PERIODIC, wide, &r.variant, &r.tw, &r.th);  // DIRECT
     }
     r.dx = d.dx;
     r.dy = d.dy;
@@ -736,7 +748,7 @@ int ws_attach_medium(ws_ctx *c, void *medium, int64_t bytes) {
   for (int k = 0; k < c->n_patches; ++k) {
     PatchRow &r = c->rows[k];
     const bool march = r.mx >= kMarchWidth - 4 && march_fits(r.plane, c->dtype);
-    default_tile(r.mx, r.my, march ? r.bc : WS_BC_PERIODIC, &r.variant, &r.tw, &r.th);
+    default_tile(r.mx, r.my, march ? r.bc : WS_BC_PERIODIC, kMarchWide, &r.variant, &r.tw, &r.th);
   }
   segment_rows(c->rows, c->n_cu);
   c->drop_graph();
@@ -1663,7 +1675,7 @@ int ws_cf_init(ws_cf **out, ws_ctx *coarse, ws_ctx *fine, int32_t ratio,
     cf->max_step_blocks = std::max(
         cf->max_step_blocks, cf_step_blocks_host(d.mx, d.my, pl[k].ncx, pl[k].ncy, true, cf->strip));
     cf->max_finish_blocks =
-        std::max(cf->max_finish_blocks, cf_finish_blocks_host(pl[k].ncx, pl[k].ncy));
+        std::max(cf->max_finish_blocks, cf_finish_blocks_host(pl[k].ncx, pl[k].ncy, ratio));
   }
   if (hipMemcpyAsync(cf->ws + cf->off_place, pl.data(), pl.size() * sizeof(CfPlace),
                      hipMemcpyHostToDevice, coarse->stream) != hipSuccess ||

@@ -190,7 +190,7 @@ int cf_step_blocks_host(int mx, int my, int ncx, int ncy, bool coarse, int strip
 // Edges per block of the fine-step kernel for fine patches of at most
 // max_side cells per side: a multiple of 64, at most 256.
 int cf_strip_host(int max_side);
-int cf_finish_blocks_host(int ncx, int ncy);
+int cf_finish_blocks_host(int ncx, int ncy, int r);
 // The coarse cell outside interface edge e of a fine patch (edges numbered
 // left, right over ncy, then bottom, top over ncx).
 void cf_out_cell_host(const CfPlace &pl, int e, int &oi, int &oj);
