@@ -605,7 +605,8 @@ __global__ __launch_bounds__(kThreads) void cf_finish_kernel(CfArgs a, double dt
     }
     return;
   }
-  const int patch = (int)blockIdx.x / nav, b = (int)blockIdx.x % nav;
+  const int bx = (int)blockIdx.x;
+  const int patch = a.reverse ? a.n_fine - 1 - bx / nav : bx / nav, b = bx % nav;
   const CfPlace pl = a.place[patch];
   if (b >= cf_finish_blocks(pl.ncx, pl.ncy, r)) return;
   const PatchRow cp = a.cpatch[pl.coarse];

@@ -355,6 +355,10 @@ struct ws_ctx {
     a.n_tiles = (int32_t)tiles.size();
     a.tile_base = 0;
     a.persistent = 1;
+    // steps alternate between the pools, and with them the order of the tiles:
+    // what a launch wrote last is what the next one reads first, while the
+    // Infinity Cache still holds it
+    a.reverse = src;
     a.packs = reinterpret_cast<const PackWave *>(ws + L.packs);
     a.qin = pool[src];
     a.qout = pool[1 - src];
@@ -1739,6 +1743,7 @@ int ws_cf_step(ws_cf *cf, double dt) {
   }
   // updating and the conservation fix, then the coarse physical ghosts
   a.f_cur = f->pool[f->cur];
+  a.reverse = f->cur;  // as the fine level's next step would go
   HIPCHK(launch_cf_finish(c->dtype, a, dt, cf->max_finish_blocks, c->stream));
   return ws_fill_ghosts(c);
 }

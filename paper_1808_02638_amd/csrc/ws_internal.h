@@ -33,6 +33,7 @@ struct StepArgs {
   int32_t n_tiles;
   int32_t tile_base;   // direct mode: first tile of this launch
   int32_t persistent;  // 1: persistent launch over all tiles; 0: tile = base + blockIdx
+  int32_t reverse;     // 1: every run of tiles from its last to its first
   const void *qin;
   void *qout;
   int32_t pool_bytes;  // bytes of each pool (PACKED tiles: below 2^31)
@@ -165,6 +166,7 @@ struct CfArgs {
   const InstRow *cinst, *finst;
   const CfPlace *place;             // [n_fine]
   int32_t n_fine, r;
+  int32_t reverse;    // 1: cf_finish takes the fine patches from last to first
   const void *c_old;  // coarse state at t_n
   void *c_new;        // coarse state after the coarse step (updated in place)
   void *f_cur;        // fine current state

@@ -1457,7 +1457,8 @@ __device__ __attribute__((always_inline)) inline void step_body(const StepArgs &
   const int in_group = G / groups + (x < G % groups ? 1 : 0);
   const int beg = (int)((int64_t)a.n_tiles * x / groups);
   const int end = (int)((int64_t)a.n_tiles * (x + 1) / groups);
-  for (int t = beg + y; t < end; t += in_group) {
+  for (int u = beg + y; u < end; u += in_group) {
+    const int t = a.reverse ? beg + end - 1 - u : u;
     int inst = 0;
     double m = do_unit<T, LIM, MASKS, VARS, TC, VAR>(a, t, wave, inst);
     if constexpr (VAR) m = tile_max(m, lane, wave);

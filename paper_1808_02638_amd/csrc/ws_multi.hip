@@ -495,8 +495,10 @@ __global__ __launch_bounds__(kThreads, (two_waves<T, LIM, MASKS, DOMAIN>())) voi
     return;
   }
   const int x = (int)blockIdx.x % kGroups, y = (int)blockIdx.x / kGroups;
-  const int t = (int)((int64_t)a.n_tiles * x / kGroups) + y;
-  if (t >= (int)((int64_t)a.n_tiles * (x + 1) / kGroups)) return;
+  const int beg = (int)((int64_t)a.n_tiles * x / kGroups);
+  const int end = (int)((int64_t)a.n_tiles * (x + 1) / kGroups);
+  if (beg + y >= end) return;
+  const int t = a.reverse ? end - 1 - y : beg + y;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const TileEntry te = uniform_row(a.tiles[t]);
   const PatchRow pr = uniform_row(a.patches[te.patch]);
