@@ -217,8 +217,8 @@ __device__ inline float recip(float x) {
 template <typename T>
 __device__ inline void var_strengths(T Zl, T Zr, T dp, T dn, T &a1, T &a2, T &iz) {
   iz = recip(Zl + Zr);
-  a1 = (Zr * dn - dp) * iz;
-  a2 = (dp + Zl * dn) * iz;
+  a1 = fma(Zr, dn, -dp) * iz;
+  a2 = fma(Zl, dn, dp) * iz;
 }
 
 // Limited strengths at the edge (l, r) given the upwind strengths a1u (edge
@@ -226,7 +226,7 @@ __device__ inline void var_strengths(T Zl, T Zr, T dp, T dn, T &a1, T &a2, T &iz
 template <typename T, int LIM>
 __device__ inline void var_limited(T a1, T a2, T a1u, T a2u, T Zl, T Zr, T wl, T wr, T &l1,
                                    T &l2) {
-  const T zz = Zl * Zr + T(1);
+  const T zz = fma(Zl, Zr, T(1));
   l1 = limited<T, LIM>(a1, a1u * (zz * wl));
   l2 = limited<T, LIM>(a2, a2u * (zz * wr));
 }
@@ -235,9 +235,9 @@ __device__ inline void var_limited(T a1, T a2, T a1u, T a2u, T Zl, T Zr, T wl, T
 template <typename T, int LIM>
 __device__ inline void var_corr(T cl, T Zl, T cr, T Zr, T l1, T l2, T dtdx, T &Fp, T &Fn) {
   constexpr T half = T(0.5 * limiter_scale(LIM));
-  const T gl = half * cl * (T(1) - cl * dtdx), gr = half * cr * (T(1) - cr * dtdx);
-  Fp = gr * Zr * l2 - gl * Zl * l1;
-  Fn = gl * l1 + gr * l2;
+  const T w1 = half * cl * fma(-cl, dtdx, T(1)) * l1, w2 = half * cr * fma(-cr, dtdx, T(1)) * l2;
+  Fp = fma(Zr, w2, -(Zl * w1));
+  Fn = w1 + w2;
 }
 
 // One direction of a cell's update in a heterogeneous medium, from the five
@@ -291,23 +291,23 @@ template <typename T>
 __device__ inline void var_combine(const VarLine<T> &X, const VarLine<T> &Y, T Xpb, T Xpt, T Ypl,
                                    T Ypr, T p0, T u0, T v0, T dtdx, T dtdy, T &pn, T &un, T &vn,
                                    T &cfl) {
-  const T c0 = X.c0, Z0 = X.z0;
-  const T Xp0 = c0 * Z0 * X.xs, Yp0 = c0 * Z0 * Y.xs;
+  const T c0 = X.c0, K0 = X.c0 * X.z0;  // c Z of the cell; of its neighbours below
+  const T Xp0 = K0 * X.xs, Yp0 = K0 * Y.xs;
   T h = T(0.5) * dtdy * X.izl;
-  const T FLp = X.Fl_p - h * (X.c0 * X.z0 * Ypl - X.cl * X.zl * Yp0);
-  const T FLu = X.Fl_n - h * (X.c0 * Ypl + X.cl * Yp0);
+  const T FLp = fma(-h, fma(K0, Ypl, -(X.cl * X.zl * Yp0)), X.Fl_p);
+  const T FLu = fma(-h, fma(c0, Ypl, X.cl * Yp0), X.Fl_n);
   h = T(0.5) * dtdy * X.izr;
-  const T FRp = X.Fr_p - h * (X.cr * X.zr * Yp0 - X.c0 * X.z0 * Ypr);
-  const T FRu = X.Fr_n - h * (X.cr * Yp0 + X.c0 * Ypr);
+  const T FRp = fma(-h, fma(X.cr * X.zr, Yp0, -(K0 * Ypr)), X.Fr_p);
+  const T FRu = fma(-h, fma(X.cr, Yp0, c0 * Ypr), X.Fr_n);
   h = T(0.5) * dtdx * Y.izl;
-  const T GBp = Y.Fl_p - h * (Y.c0 * Y.z0 * Xpb - Y.cl * Y.zl * Xp0);
-  const T GBv = Y.Fl_n - h * (Y.c0 * Xpb + Y.cl * Xp0);
+  const T GBp = fma(-h, fma(K0, Xpb, -(Y.cl * Y.zl * Xp0)), Y.Fl_p);
+  const T GBv = fma(-h, fma(c0, Xpb, Y.cl * Xp0), Y.Fl_n);
   h = T(0.5) * dtdx * Y.izr;
-  const T GTp = Y.Fr_p - h * (Y.cr * Y.zr * Xp0 - Y.c0 * Y.z0 * Xpt);
-  const T GTv = Y.Fr_n - h * (Y.cr * Xp0 + Y.c0 * Xpt);
-  pn = p0 - dtdx * (Xp0 + (FRp - FLp)) - dtdy * (Yp0 + (GTp - GBp));
-  un = u0 - dtdx * (c0 * X.xd + (FRu - FLu));
-  vn = v0 - dtdy * (c0 * Y.xd + (GTv - GBv));
+  const T GTp = fma(-h, fma(Y.cr * Y.zr, Xp0, -(K0 * Xpt)), Y.Fr_p);
+  const T GTv = fma(-h, fma(Y.cr, Xp0, c0 * Xpt), Y.Fr_n);
+  pn = p0 - fma(dtdy, Yp0 + (GTp - GBp), dtdx * (Xp0 + (FRp - FLp)));
+  un = fma(-dtdx, fma(c0, X.xd, FRu - FLu), u0);
+  vn = fma(-dtdy, fma(c0, Y.xd, GTv - GBv), v0);
   cfl = fmax(fmax(fmax(X.cl, X.c0), X.cr) * dtdx, fmax(fmax(Y.cl, Y.c0), Y.cr) * dtdy);
 }
 
