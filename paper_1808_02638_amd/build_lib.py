@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 # (source, object, extra flags): the step kernels compile in seven parts
 SOURCES = [("ws_kernels.hip", f"ws_kernels_{n}.o", [f"-DWS_PART={n}"]) for n in range(7)] + [
-    (f"ws_{n}.hip", f"ws_{n}.o", []) for n in ("multi", "adjoint", "amr", "api")]
+    (f"ws_{n}.hip", f"ws_{n}.o", []) for n in ("multi", "block", "adjoint", "amr", "api")]
 LIB = os.path.join(HERE, "libwavestep.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

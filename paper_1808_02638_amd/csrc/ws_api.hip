@@ -293,6 +293,8 @@ struct ws_ctx {
   std::vector<PackWave> packs;  // wavefronts of the PACKED tiles
   std::vector<TileEntry> two_tiles;  // tiles of the two-step launch (empty: it does not apply)
   int two_rows = 0;                  // rows per segment of theirs
+  int n_block = 0;  // tiles of the four-step launch (0: it does not apply)
+  std::vector<TileEntry> block_tiles;  // their list (a level of one patch needs none)
   // a tiled level cut along full columns and rows: its cuts, and the patch of
   // each place (empty: cut otherwise)
   std::vector<int32_t> xcut, ycut, place;
@@ -413,6 +415,8 @@ struct ws_ctx {
   // the tile list, where the level takes one and they fit.
   void build_two_tiles() {
     two_tiles.clear();
+    block_tiles.clear();
+    n_block = 0;
     if (medium || (limiter & WS_TRANSVERSE_CORR)) return;
     const bool domain = !place.empty();
     if (link_src && !domain) return;
@@ -457,6 +461,20 @@ struct ws_ctx {
     else
       for (int k : order) add(k, rows[k].mx, rows[k].my);
     domain_off = L.tiles + round_up((int64_t)(tiles.size() + two_tiles.size()) * sizeof(TileEntry), 16);
+    // The four-step launch's tiles, after those, on levels of at most one per
+    // CU: with more, the fourfold arithmetic of its regions costs more than
+    // the launches it saves.
+    if (domain) return;
+    int64_t n = 0;
+    for (const PatchRow &r : rows) n += ceil_div(r.mx, kBlockCells) * ceil_div(r.my, kBlockCells);
+    if (n > n_cu) return;
+    if (n_patches > 1 && (int64_t)(tiles.size() + two_tiles.size()) + n > L.max_tiles) return;
+    n_block = (int)n;
+    if (n_patches == 1) return;
+    for (int k : order)
+      for (int ty = 0; ty < ceil_div(rows[k].my, kBlockCells); ++ty)
+        for (int tx = 0; tx < ceil_div(rows[k].mx, kBlockCells); ++tx)
+          block_tiles.push_back(TileEntry{k, (uint16_t)tx, (uint16_t)ty});
   }
 
   // Upload the two-step launch's tables (the stream is synchronised after).
@@ -464,6 +482,10 @@ struct ws_ctx {
     if (two_tiles.empty()) return WS_OK;
     HIPCHK(hipMemcpyAsync(ws + L.tiles + tiles.size() * sizeof(TileEntry), two_tiles.data(),
                           two_tiles.size() * sizeof(TileEntry), hipMemcpyHostToDevice, stream));
+    if (!block_tiles.empty())
+      HIPCHK(hipMemcpyAsync(ws + L.tiles + (tiles.size() + two_tiles.size()) * sizeof(TileEntry),
+                            block_tiles.data(), block_tiles.size() * sizeof(TileEntry),
+                            hipMemcpyHostToDevice, stream));
     if (place.empty()) return WS_OK;
     const int64_t es = dtype == WS_F32 ? 4 : 8;
     std::vector<DomainPatch> tab;
@@ -1065,6 +1087,40 @@ static int enqueue_two(ws_ctx *c, int src, double cfl_desired) {
   return WS_OK;
 }
 
+// kBlockSteps steps in one launch, from pool `src` into the other.
+static int enqueue_block(ws_ctx *c, int src, double cfl_desired) {
+  StepArgs a = c->step_args(src, 0.0, cfl_desired);
+  a.tiles = c->n_patches == 1 ? nullptr : c->d_tiles() + c->tiles.size() + c->two_tiles.size();
+  a.n_tiles = c->n_block;
+  HIPCHK(launch_step_block(c->dtype, c->limiter, a, c->stream));
+  return WS_OK;
+}
+
+// Launches of a captured loop of n steps: blocks of four, pairs, single steps.
+struct LoopPlan {
+  int blocks = 0, pairs = 0, singles = 0;
+};
+
+// The fewest launches that leave the state in the pool (and its time-step
+// slot) that n single steps leave it in, so an even number of blocks and
+// pairs, and that end with a single step, so that the other pool holds the
+// state before it and every reported Courant number is that step's.
+static LoopPlan plan_loop(const ws_ctx *c, int n) {
+  LoopPlan best{0, 0, n};
+  if (c->two_tiles.empty()) return best;
+  best = LoopPlan{0, (n - 1) / 4 * 2, n - (n - 1) / 4 * 4};
+  if (c->n_block == 0) return best;
+  for (int pairs = 0; pairs <= 3; ++pairs)
+    for (int singles = 1; singles <= 8; ++singles) {
+      const int rest = n - 2 * pairs - singles;
+      if (rest < 0 || rest % kBlockSteps) continue;
+      const LoopPlan p{rest / kBlockSteps, pairs, singles};
+      if ((p.blocks + p.pairs) % 2) continue;
+      if (p.blocks + p.pairs + p.singles < best.blocks + best.pairs + best.singles) best = p;
+    }
+  return best;
+}
+
 int ws_step_auto(ws_ctx *c, double cfl_desired) {
   if (!c) return fail(WS_EINVAL, "ctx is NULL");
   if (!(cfl_desired > 0.0) || !std::isfinite(cfl_desired))
@@ -1083,18 +1139,15 @@ int ws_capture_steps(ws_ctx *c, int32_t n_steps, double cfl_desired) {
   HIPCHK(hipStreamSynchronize(c->stream));
   HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
   int rc = WS_OK;
-  // Pairs of steps in one launch where the level takes them.  Their number is
-  // even, so that the state ends in the pool (and its time-step slot) that
-  // n_steps single steps leave it in, and the last step is a single one, so
-  // that the other pool holds the state before it and every reported Courant
-  // number is that step's.
-  const int pairs = c->two_tiles.empty() ? 0 : (n_steps - 1) / 4 * 2;
+  const LoopPlan plan = plan_loop(c, n_steps);
   int src = c->cur;
-  for (int s = 0; s < pairs && rc == WS_OK; ++s, src = 1 - src)
+  for (int s = 0; s < plan.blocks && rc == WS_OK; ++s, src = 1 - src)
+    rc = enqueue_block(c, src, cfl_desired);
+  for (int s = 0; s < plan.pairs && rc == WS_OK; ++s, src = 1 - src)
     rc = enqueue_two(c, src, cfl_desired);
   // pairs of steps of a tiled level leave its ghosts to the first single one
-  if (pairs > 0 && rc == WS_OK) rc = link_after_step(c, src);
-  for (int s = 2 * pairs; s < n_steps && rc == WS_OK; ++s, src = 1 - src)
+  if (plan.pairs > 0 && rc == WS_OK) rc = link_after_step(c, src);
+  for (int s = 0; s < plan.singles && rc == WS_OK; ++s, src = 1 - src)
     rc = enqueue_auto(c, src, cfl_desired);
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(c->stream, &g);

@@ -39,8 +39,9 @@ __device__ inline float uniform(float v) {
   return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
 }
 
+// lane_coef: each lane's own; make_coef: those of a wave-uniform dt.
 template <typename T, int LIM = WS_LIM_NONE>
-__device__ inline Coef<T> make_coef(double c, double Z, double dt, double dx, double dy) {
+__device__ inline Coef<T> lane_coef(double c, double Z, double dt, double dx, double dy) {
   const double dtdx = dt / dx, dtdy = dt / dy, iz = 1.0 / Z;
   const double fx = 0.25 * c * (1.0 - c * dtdx), fy = 0.25 * c * (1.0 - c * dtdy);
   const double gx = 0.125 * dtdx * c * c, gy = 0.125 * dtdy * c * c;
@@ -65,6 +66,12 @@ __device__ inline Coef<T> make_coef(double c, double Z, double dt, double dx, do
   k.ly = (T)(limiter_scale(LIM) * fy);
   k.tx = (T)(limiter_scale(LIM) * (1.0 - c * dtdx));
   k.ty = (T)(limiter_scale(LIM) * (1.0 - c * dtdy));
+  return k;
+}
+
+template <typename T, int LIM = WS_LIM_NONE>
+__device__ inline Coef<T> make_coef(double c, double Z, double dt, double dx, double dy) {
+  Coef<T> k = lane_coef<T, LIM>(c, Z, dt, dx, dy);
   T *f = &k.Z;
   for (int n = 0; n < (int)(sizeof(Coef<T>) / sizeof(T)); ++n) f[n] = uniform(f[n]);
   return k;

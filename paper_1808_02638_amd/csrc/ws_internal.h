@@ -70,7 +70,11 @@ hipError_t launch_step(int dtype, int limiter, int vars, const StepArgs &a, int 
 // kMultiCols columns by 4 seg_rows rows; a.dt_override > 0 fixes dt, else
 // a.cfl_desired > 0 rescales it after each of the two steps.
 hipError_t launch_step_two(int dtype, int limiter, const StepArgs &a, hipStream_t s);
-// Workgroups of that launch a CU holds at once (0: unknown).
+// kBlockSteps steps in one launch (ws_block.hip): small levels of patches with
+// extrapolation boundaries; a.tiles are kBlockCells x kBlockCells cells
+// (nullptr: those of the only patch, row by row).
+hipError_t launch_step_block(int dtype, int limiter, const StepArgs &a, hipStream_t s);
+// Workgroups of a two-step launch a CU holds at once (0: unknown).
 int step_two_occupancy(int dtype, int limiter, bool domain);
 // The ghost ring of an mx x my patch in one numbering, shared by the kernels
 // that walk it and the host tables indexed by it: rows -2, -1 across the

@@ -609,8 +609,11 @@ struct MarchLanes {
     }
     put(pn, un, vn, r);
     if (ybc && (r == 0 || r == my - 1)) {
-      const int g0 = r == 0 ? -2 : my;
-      for (int g = g0; g <= g0 + 1; ++g) put(pn, un, vn, g);
+      // (both ends where the patch has one row)
+      if (r == 0)
+        for (int g = -2; g < 0; ++g) put(pn, un, vn, g);
+      if (r == my - 1)
+        for (int g = my; g <= my + 1; ++g) put(pn, un, vn, g);
     }
   }
 };

@@ -25,6 +25,8 @@ constexpr int kMarchWidth = 64;  // MARCH segments are one wavefront wide
 constexpr int kMultiHalo = 4;    // halo lanes per side of a two-step segment
 constexpr int kMultiCols = kMarchWidth - 2 * kMultiHalo;  // columns it updates
 constexpr int kMaxTwoRows = 26;  // rows of one (longer ones leave too few wavefronts)
+constexpr int kBlockSteps = 4;   // steps of a four-step launch
+constexpr int kBlockCells = 16;  // cells per side of its tiles
 constexpr int kSumTile = 64;     // conservation sums: tiles of 64 x 64 cells
 
 // One wavefront of a PACKED tile: up to kMaxPieces column blocks (patch,

@@ -1,7 +1,7 @@
-"""Two steps per launch in captured loops: the same bits as single steps.
+"""Several steps per launch in captured loops: the same bits as single steps.
 
 A captured loop of a level whose patches have extrapolation boundaries takes
-pairs of steps in one launch.  State, ghosts, the other pool (the state one
+pairs of steps in one launch, and on a small level four.  State, ghosts, the other pool (the state one
 step earlier), time steps and Courant numbers equal those of as many eager
 single steps, bit for bit, at the edges of the pairing (1 .. 8 steps), of the
 56-column segments and of the rows that a segment shares with its neighbours.
@@ -43,6 +43,7 @@ def _pair(ws, sizes, dtype, limiter):
 
 
 def _same(a, b):
+    torch.cuda.synchronize()  # the levels run on streams of their own
     pools = [(lev.pools[w].view(lev.dtype)) for lev in (a, b)
              for w in (lev.current_pool(), 1 - lev.current_pool())]
     for k in range(a.n):
@@ -57,20 +58,37 @@ def _same(a, b):
 @pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
 @pytest.mark.parametrize("limiter", ["mc", "vanleer", "none"])
 @pytest.mark.parametrize("sizes", [[(1, 1)], [(2, 3)], [(5, 1)], [(56, 33)], [(57, 64)],
-                                   [(113, 18), (60, 5), (24, 200)], [(300, 211)]])
-def test_pairs_equal_single_steps(ws, sizes, limiter, dtype):
-    a, b = _pair(ws, sizes, dtype, limiter)
-    a.capture(8, 0.9)
+                                   [(16, 17), (31, 8)], [(113, 18), (60, 5), (24, 200)],
+                                   [(256, 255)]])
+@pytest.mark.parametrize("small", [True, False])
+def test_pairs_equal_single_steps(ws, small, sizes, limiter, dtype):
+    # at most 256 tiles of 16 x 16 cells: four steps per launch; else pairs
+    a, b = _pair(ws, sizes if small else sizes + [(272, 260)], dtype, limiter)
+    a.capture(18, 0.9)
     for _ in range(2):  # a replay, with eager reads between
         a.graph_launch()
-        for _ in range(8):
+        for _ in range(18):
             b.step_auto(0.9)
         _same(a, b)
 
 
-@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7])
-def test_every_remainder_of_the_pairing(ws, n):
-    a, b = _pair(ws, [(130, 77)], torch.float64, "mc")
+@pytest.mark.parametrize("tile", [("march", 64, 4), ("march", 64, 16), ("direct", 64, 4)])
+def test_one_row_patch_has_both_ghost_sides(ws, tile):
+    """MARCH tiles of a patch with one row write its ghosts above as well."""
+    a, b = _pair(ws, [(70, 1)], torch.float64, "mc")
+    a.set_tiling(tile[1], tile[2], variant=tile[0])
+    b.set_tiling(32, 8, variant="direct")
+    for lev in (a, b):
+        lev.set_dt([0.2])
+        for _ in range(5):
+            lev.step(0.002)
+    _same(a, b)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 9, 10, 11, 12, 13, 16])
+@pytest.mark.parametrize("shape", [(130, 77), (300, 211)])
+def test_every_remainder_of_the_pairing(ws, shape, n):
+    a, b = _pair(ws, [shape], torch.float64, "mc")
     a.capture(n, 0.9)
     a.graph_launch()
     for _ in range(n):
