@@ -462,12 +462,14 @@ struct ws_ctx {
       for (int k : order) add(k, rows[k].mx, rows[k].my);
     domain_off = L.tiles + round_up((int64_t)(tiles.size() + two_tiles.size()) * sizeof(TileEntry), 16);
     // The four-step launch's tiles, after those, on levels of at most one per
-    // CU: with more, the fourfold arithmetic of its regions costs more than
-    // the launches it saves.
+    // CU (FP32: two): with more, the arithmetic of its regions, most of them
+    // halo, costs more than the launches it saves.  us per step in loops of 100,
+    // with four and with two steps per launch: FP64 256^2 (256 tiles) 2.3 and
+    // 3.5, 350 x 360 (506 tiles) 3.8 and 3.6; FP32 1.7 and 3.1, 2.5 and 3.2.
     if (domain) return;
     int64_t n = 0;
     for (const PatchRow &r : rows) n += ceil_div(r.mx, kBlockCells) * ceil_div(r.my, kBlockCells);
-    if (n > n_cu) return;
+    if (n > (dtype == WS_F32 ? 2 : 1) * (int64_t)n_cu) return;
     if (n_patches > 1 && (int64_t)(tiles.size() + two_tiles.size()) + n > L.max_tiles) return;
     n_block = (int)n;
     if (n_patches == 1) return;

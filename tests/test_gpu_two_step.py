@@ -62,8 +62,9 @@ def _same(a, b):
                                    [(256, 255)]])
 @pytest.mark.parametrize("small", [True, False])
 def test_pairs_equal_single_steps(ws, small, sizes, limiter, dtype):
-    # at most 256 tiles of 16 x 16 cells: four steps per launch; else pairs
-    a, b = _pair(ws, sizes if small else sizes + [(272, 260)], dtype, limiter)
+    # few tiles of 16 x 16 cells (one per CU in FP64): four steps per launch;
+    # else pairs
+    a, b = _pair(ws, sizes if small else sizes + [(400, 340)], dtype, limiter)
     a.capture(18, 0.9)
     for _ in range(2):  # a replay, with eager reads between
         a.graph_launch()
