@@ -631,7 +631,9 @@ static int setup_level(ws_ctx *c, const ws_patch_desc *patches, int32_t n_patche
     cells += n;
     if (patches[k].mx < kMarchWide) narrow += n;
   }
-  const int wide = 4 * narrow < cells ? 1 : kMarchWide;
+  // Only on levels of many patches: a few patches are bound by one tile's time,
+  // and a narrow patch's cells take less of it as DIRECT tiles.
+  const int wide = n_patches >= 64 && 4 * narrow < cells ? 1 : kMarchWide;
   for (int k = 0; k < n_patches; ++k) {
     PatchRow &r = c->rows[k];
     const ws_patch_desc &d = patches[k];
