@@ -231,7 +231,9 @@ int ws_set_dt(ws_ctx *ctx, const double *dt_per_instance);
 int ws_step_auto(ws_ctx *ctx, double cfl_desired);
 
 /* Capture n_steps of ws_step_auto in a hipGraph (replacing any previous one).
- * Needs n_steps >= 1. */
+ * Needs n_steps >= 1.  Several steps may share a launch; the results are those
+ * of n_steps calls bit for bit, also where the state holds other ghosts than
+ * those of the boundary condition (the first step reads them as they are). */
 int ws_capture_steps(ws_ctx *ctx, int32_t n_steps, double cfl_desired);
 
 /* Launch the captured graph on the context's stream.  Asynchronous. */

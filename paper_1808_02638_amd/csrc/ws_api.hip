@@ -1100,25 +1100,31 @@ static int enqueue_block(ws_ctx *c, int src, double cfl_desired) {
   return WS_OK;
 }
 
-// Launches of a captured loop of n steps: blocks of four, pairs, single steps.
+// Launches of a captured loop of n steps: a single step, blocks of four, pairs,
+// single steps.
 struct LoopPlan {
-  int blocks = 0, pairs = 0, singles = 0;
+  int lead = 0, blocks = 0, pairs = 0, singles = 0;
 };
 
 // The fewest launches that leave the state in the pool (and its time-step
 // slot) that n single steps leave it in, so an even number of blocks and
 // pairs, and that end with a single step, so that the other pool holds the
-// state before it and every reported Courant number is that step's.
+// state before it and every reported Courant number is that step's.  A pair of
+// steps of a tiled level reads its neighbour patches' cells in place of the
+// ghosts, so a single step, which reads the ghosts as the state holds them and
+// leaves the exchanged ones, goes first.
 static LoopPlan plan_loop(const ws_ctx *c, int n) {
-  LoopPlan best{0, 0, n};
+  LoopPlan best{0, 0, 0, n};
   if (c->two_tiles.empty()) return best;
-  best = LoopPlan{0, (n - 1) / 4 * 2, n - (n - 1) / 4 * 4};
+  const int lead = c->place.empty() ? 0 : 1, rest = n - lead;
+  if (rest < 5) return best;
+  best = LoopPlan{lead, 0, (rest - 1) / 4 * 2, rest - (rest - 1) / 4 * 4};
   if (c->n_block == 0) return best;
   for (int pairs = 0; pairs <= 3; ++pairs)
     for (int singles = 1; singles <= 8; ++singles) {
-      const int rest = n - 2 * pairs - singles;
-      if (rest < 0 || rest % kBlockSteps) continue;
-      const LoopPlan p{rest / kBlockSteps, pairs, singles};
+      const int in_blocks = rest - 2 * pairs - singles;
+      if (in_blocks < 0 || in_blocks % kBlockSteps) continue;
+      const LoopPlan p{lead, in_blocks / kBlockSteps, pairs, singles};
       if ((p.blocks + p.pairs) % 2) continue;
       if (p.blocks + p.pairs + p.singles < best.blocks + best.pairs + best.singles) best = p;
     }
@@ -1145,6 +1151,8 @@ int ws_capture_steps(ws_ctx *c, int32_t n_steps, double cfl_desired) {
   int rc = WS_OK;
   const LoopPlan plan = plan_loop(c, n_steps);
   int src = c->cur;
+  for (int s = 0; s < plan.lead && rc == WS_OK; ++s, src = 1 - src)
+    rc = enqueue_auto(c, src, cfl_desired);
   for (int s = 0; s < plan.blocks && rc == WS_OK; ++s, src = 1 - src)
     rc = enqueue_block(c, src, cfl_desired);
   for (int s = 0; s < plan.pairs && rc == WS_OK; ++s, src = 1 - src)

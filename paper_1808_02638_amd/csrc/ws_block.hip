@@ -75,7 +75,8 @@ __global__ __launch_bounds__(kBlockThreads) void step_kernel_block(StepArgs a) {
   const int i0 = te.tx * kBlockCells - 2 * kBlockSteps, j0 = te.ty * kBlockCells - 2 * kBlockSteps;
   const int i = i0 + x, j = j0 + y;
   // the interior cell this one is (itself, or the one its ghost copies), in
-  // the region's numbering, and the one below it
+  // the region's numbering, and the one below it; the first step reads the
+  // ghosts as the state holds them
   const int ci = min(max(i, 0), mx - 1), cj = min(max(j, 0), my - 1);
   const int cx = ci - i0, cy = min(max(cj - j0, 0), kSide - 1);
   const int by = min(max(min(max(j - 1, 0), my - 1) - j0, 0), kSide - 1);
@@ -83,7 +84,8 @@ __global__ __launch_bounds__(kBlockThreads) void step_kernel_block(StepArgs a) {
   const bool ghost = i != ci || j != cj;
   const bool ghosts = i0 < 0 || j0 < 0 || i0 + kSide > mx || j0 + kSide > my;  // of the workgroup
   const int64_t org = pr.q_off + 2 * (int64_t)pr.ld + pr.col0;
-  const T *q = reinterpret_cast<const T *>(a.qin) + org + (int64_t)cj * pr.ld + ci;
+  const T *q = reinterpret_cast<const T *>(a.qin) + org +
+               (int64_t)min(max(j, -2), my + 1) * pr.ld + min(max(i, -2), mx + 1);
   T p = q[0], u = q[pr.plane], v = q[2 * pr.plane];
   if (tid < kBlockSteps) {
     // lane s: the coefficients of step s
@@ -99,8 +101,9 @@ __global__ __launch_bounds__(kBlockThreads) void step_kernel_block(StepArgs a) {
     __syncthreads();
     const Coef<T> k = uniform_row(S.k[s]);
     const T Z = k.Z;
-    if (ghosts && ghost) p = S.p[cy][cxr], u = S.u[cy][cxr], v = S.v[cy][cxr];
-    const T pb = S.p[by][cxr], vb = S.v[by][cxr];
+    if (ghosts && ghost && s > 0) p = S.p[cy][cxr], u = S.u[cy][cxr], v = S.v[cy][cxr];
+    const int yb = s > 0 ? by : ym, xb = s > 0 ? cxr : x;
+    const T pb = S.p[yb][xb], vb = S.v[yb][xb];
     // left x-edge and bottom y-edge of the cell
     const T dp = p - shr(p), du = u - shr(u);
     const T a1L = s1(Z, dp, du), a2L = s2(Z, dp, du);

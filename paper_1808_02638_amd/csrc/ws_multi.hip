@@ -124,10 +124,11 @@ __device__ inline void nearest_columns(Row3<T> &N, int lo, int hi, bool glo, boo
 }
 
 // Lanes of one segment: lane l holds column i of the patch, lanes kMultiHalo
-// .. 63 - kMultiHalo are updated.  Reads take the nearest interior cell (the
-// extrapolation ghosts).  Rows are addressed by a scalar offset that is
-// stepped along, columns by the lane's: no vector instruction goes into
-// addresses.
+// .. 63 - kMultiHalo are updated.  The first step reads the ghosts as the state
+// holds them (they need not be extrapolated: a state may be uploaded with
+// others); the lanes and rows past them read the last ones.  Rows are addressed
+// by a scalar offset that is stepped along, columns by the lane's: no vector
+// instruction goes into addresses.
 template <typename T>
 struct MultiLanes {
   __amdgpu_buffer_rsrc_t ib, ob;  // the patch in the two pools, from padded cell (-2, -2)
@@ -147,14 +148,14 @@ struct MultiLanes {
     my = pr.my;
     r0 = r0_;
     r1 = r1_;
-    rmax = min(r1 + 3, pr.my - 1);
+    rmax = min(r1 + 3, pr.my + 1);
     const int64_t first = 2 * (int64_t)pr.ld + 2;
     ib = __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(qi - first), 0, (int)(3 * plb),
                                            kRawBufferWord3);
     ob = __builtin_amdgcn_make_buffer_rsrc(qo - first, 0, (int)(3 * plb), kRawBufferWord3);
     i = i0 + l;
     mx = pr.mx;
-    colb = (unsigned)(min(max(i, 0), mx - 1) + 2) * (unsigned)sizeof(T);
+    colb = (unsigned)(min(max(i, -2), mx + 1) + 2) * (unsigned)sizeof(T);
     lo = -i0;
     hi = mx - 1 - i0;
     glo = i < 0;
@@ -173,7 +174,7 @@ struct MultiLanes {
     if (own || edge) row[0] = (uint8_t)(own ? branches : branches & 15u);
     if (r == my - 1 && (own || edge)) row[mx + 1] = (uint8_t)(own ? top : 0u);  // no edge owns the corner
   }
-  // Rows outside the patch copy its first and last row.
+  // The new rows outside the patch copy its first and last row.
   __device__ bool clamp_y() const { return true; }
   // Whether the segment holds ghost columns.
   __device__ bool ghosts() const { return lo > 0 || hi < kMarchWidth - 1; }
@@ -182,7 +183,7 @@ struct MultiLanes {
     unsigned o;
   };
   __device__ unsigned row_offset(int r) const {
-    return (unsigned)(min(max(r, 0), rmax) + 2) * ldb;
+    return (unsigned)(min(max(r, -2), rmax) + 2) * ldb;
   }
   __device__ void fetch_at(Row3<T> &S, unsigned o) const {
     S.p = bload<T>(ib, colb, o);
