@@ -901,7 +901,9 @@ int ws_link_level(ws_ctx *c, const int32_t *origins, int32_t domain_mx, int32_t 
   for (const PatchRow &r : c->rows) c->link_max_ring = std::max(c->link_max_ring, ring_size(r.mx, r.my));
   c->drop_graph();
   // whether the patches cut the domain along full columns and rows: the
-  // origins' columns times rows are then all the patches there are
+  // origins' columns times rows are then all the patches there are.  Worked as
+  // one domain, every patch steps with one cell size, so they must be equal
+  // (sizes that differ by rounding keep to single steps).
   c->xcut.clear(), c->ycut.clear(), c->place.clear();
   c->link_periodic = periodic;
   std::vector<int32_t> xs, ys;
@@ -910,7 +912,9 @@ int ws_link_level(ws_ctx *c, const int32_t *origins, int32_t domain_mx, int32_t 
     std::sort(v->begin(), v->end());
     v->erase(std::unique(v->begin(), v->end()), v->end());
   }
-  if (xs.size() * ys.size() == (size_t)c->n_patches && 
+  bool one_size = true;
+  for (const PatchRow &r : c->rows) one_size &= r.dx == r0.dx && r.dy == r0.dy;
+  if (one_size && xs.size() * ys.size() == (size_t)c->n_patches &&
       xs.size() < kMaxDomainCuts && ys.size() < kMaxDomainCuts) {
     c->place.resize(c->n_patches);
     for (int k = 0; k < c->n_patches; ++k) {
