@@ -443,6 +443,11 @@ struct ws_ctx {
       const double cost = (seg + 7) * (rounds <= 1.0 ? 0.6 + 0.4 * rounds : rounds + 0.5);
       if (seg == 4 || cost < best) best = cost, two_rows = seg;
     }
+    // a tile's position has 16 bits per direction, which a patch's tiles keep
+    // within but a domain of many patches need not
+    if (domain && (ceil_div(xcut.back(), kMultiCols) > UINT16_MAX + 1 ||
+                   ceil_div(ycut.back(), 4 * two_rows) > UINT16_MAX + 1))
+      return;
     // a tiled level's table: its patches, then its cuts
     const int64_t n_tab =
         domain ? ceil_div((int64_t)place.size() * sizeof(DomainPatch) +

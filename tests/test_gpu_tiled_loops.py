@@ -53,3 +53,15 @@ def test_cell_sizes_equal_to_rounding(ws, which):
     a, b = _pair(ws, [(70, 33), (60, 33), (70, 44), (60, 44)], cells, org, (130, 77),
                  torch.float64, 0.004)
     _loop_is_single_steps(a, b, 6)
+
+
+@pytest.mark.parametrize("axis", ["x", "y"])
+def test_domain_wider_than_tile_numbers(ws, axis):
+    """More tiles along one direction of the domain than a tile's 16-bit
+    position can number."""
+    n, m = (8, 500000) if axis == "x" else (7, 1000000)
+    one = [(m, 1) if axis == "x" else (1, m)] * n
+    org = [(m * k, 0) if axis == "x" else (0, m * k) for k in range(n)]
+    a, b = _pair(ws, one, [(0.01, 0.01)] * n, org, (n * m, 1) if axis == "x" else (1, n * m),
+                 torch.float32, 0.004)
+    _loop_is_single_steps(a, b, 6)
