@@ -234,7 +234,7 @@ __device__ inline void var_limited(T a1, T a2, T a1u, T a2u, T Zl, T Zr, T wl, T
 // Normal correction (p, normal velocity) at an edge.
 template <typename T, int LIM>
 __device__ inline void var_corr(T cl, T Zl, T cr, T Zr, T l1, T l2, T dtdx, T &Fp, T &Fn) {
-  constexpr T half = T(0.5 * limiter_scale(LIM));
+  constexpr T half = T(0.5 * limiter_scale<T>(LIM));
   const T w1 = half * cl * fma(-cl, dtdx, T(1)) * l1, w2 = half * cr * fma(-cr, dtdx, T(1)) * l2;
   Fp = fma(Zr, w2, -(Zl * w1));
   Fn = w1 + w2;
