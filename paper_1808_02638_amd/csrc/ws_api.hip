@@ -293,6 +293,7 @@ struct ws_ctx {
   std::vector<PackWave> packs;  // wavefronts of the PACKED tiles
   std::vector<TileEntry> two_tiles;  // tiles of the two-step launch (empty: it does not apply)
   int two_rows = 0;                  // rows per segment of theirs
+  bool loops = true;                 // step loops may run: their launches' tables are kept
   int n_block = 0;  // tiles of the four-step launch (0: it does not apply)
   std::vector<TileEntry> block_tiles;  // their list (a level of one patch needs none)
   // a tiled level cut along full columns and rows: its cuts, and the patch of
@@ -417,7 +418,7 @@ struct ws_ctx {
     two_tiles.clear();
     block_tiles.clear();
     n_block = 0;
-    if (medium || (limiter & WS_TRANSVERSE_CORR)) return;
+    if (!loops || medium || (limiter & WS_TRANSVERSE_CORR)) return;
     const bool domain = !place.empty();
     if (link_src && !domain) return;
     if (domain && P.elems * (dtype == WS_F32 ? 4 : 8) >= (int64_t{1} << 31)) return;
@@ -1515,6 +1516,7 @@ int ws_step_level_noalloc(const ws_patch_desc *patches, int32_t n_patches,
   char *ws = nullptr;
   if (int rc = scratch_on_device(&ws)) return rc;
   ws_ctx c;  // host metadata only; no pinned buffer, no graph
+  c.loops = false;
   if (int rc = setup_level(&c, patches, n_patches, mats, n_instances, dtype, limiter,
                            const_cast<void *>(q_in), q_out, pool_bytes, ws,
                            reinterpret_cast<hipStream_t>(hip_stream)))
