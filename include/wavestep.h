@@ -15,8 +15,10 @@
  *   - for q = (p, u, v) and the matrices A, B of Sec. 4.1 eqs. (4.1)-(4.2)
  *     (wave speeds -c, 0, +c with c = sqrt(K/rho));
  *   - the Courant number of Sec. 2.4 eq. (2.10), max over the level's edges of
- *     |s| dt/dx, reduced over all patches on the device (Sec. 3.2.2), and the
- *     time-step rule dt = nu dt_old / cfl_old of Sec. 2.5 eq. (2.11);
+ *     |s| dt/dx (in a heterogeneous medium reduced over all patches on the
+ *     device, Sec. 3.2.2; else every edge of an instance carries the same
+ *     speeds, and its smallest cell sizes give the maximum), and the time-step
+ *     rule dt = nu dt_old / cfl_old of Sec. 2.5 eq. (2.11);
  *   - physical boundaries through the two ghost layers (Sec. 2.2 item 1):
  *     zero-order extrapolation (the outflow condition of Sec. 4.1) or periodic.
  *
@@ -108,10 +110,13 @@ int ws_init_patches(ws_ctx **out, const ws_patch_desc *patches, int32_t n_patche
                     int64_t pool_bytes, void *workspace, int64_t ws_bytes,
                     void *hip_stream);
 
-/* Tiling per patch (arrays of n_patches; all NULL keeps the defaults) and
- * workgroups per CU of the persistent launch (0: the default, as many as fit
- * on a CU at the kernel's occupancy).  Every
- * tile is worked by one workgroup of 256 threads.
+/* Tiling per patch (arrays of n_patches; all NULL keeps the tiles in use) and
+ * workgroups per CU of the persistent launch (0: as many as fit on a CU at the
+ * kernel's occupancy, which is also where a level in a heterogeneous medium
+ * starts; a homogeneous one starts with 32, most tiles then having a workgroup
+ * of their own).  Every call sets the workgroups per CU.  Every
+ * tile is worked by one workgroup of 256 threads.  Launches of several steps
+ * (ws_capture_steps, ws_step_traces) cut tiles of their own.
  *   variant WS_TILE_DIRECT: tile_w x tile_h cells, tile_w in {8,16,...,256},
  *     one thread per column computing each cell from its 13-point footprint;
  *   variant WS_TILE_MARCH: tile_w = 64; four one-wavefront segments of 64
@@ -203,7 +208,9 @@ int ws_link_layout(ws_ctx *ctx, int64_t *bytes);
  * The patches must cover [0, domain_mx) x [0, domain_my) exactly, without
  * overlap, have bc WS_BC_NONE, one instance and one cell size, and the level
  * must not be the fine level of a live coupling.  periodic:
- * bit 0 for x, bit 1 for y.  buffer: caller-owned device memory of at least
+ * bit 0 for x, bit 1 for y.  Patches that cut the domain along full columns and
+ * rows, with cell sizes equal in every bit, let captured loops take two steps
+ * per launch (the results do not depend on it).  buffer: caller-owned device memory of at least
  * ws_link_layout bytes, kept for the context's lifetime; the table is built on
  * the host and uploaded (synchronises the stream).  Drops a captured graph.
  * WS_EINVAL on a layout that does not tile the domain, WS_ENOMEM on a short
@@ -214,8 +221,9 @@ int ws_link_level(ws_ctx *ctx, const int32_t *origins, int32_t domain_mx, int32_
 /* One step of every patch with the same dt, in ONE persistent launch over the
  * level's tile list.  Writes the other pool's interior (and physical ghosts),
  * then makes it current.  *cfl_out (may be NULL) receives the level's Courant
- * number max |s| dt/dx over all edges, reduced in FP64 on the device; this
- * call synchronises the stream to return it.  dt is not checked against the
+ * number max |s| dt/dx over all edges in FP64 (read back from the device in a
+ * heterogeneous medium, else formed on the host by the same operations); with
+ * it, this call synchronises the stream.  dt is not checked against the
  * CFL limit: a caller may reject cfl > 1 and redo the step from a saved state. */
 int ws_step_level(ws_ctx *ctx, double dt, double *cfl_out);
 

@@ -2,7 +2,8 @@
 
 Patches are grouped into size classes; for each class (largest total cell
 count first) the tuner times candidate tilings (HIP events on the level's
-stream around back-to-back level steps, as a captured step loop runs them),
+stream around back-to-back single level steps; a captured loop's launches of
+several steps cut tiles of their own, and a tiling shapes its single steps),
 keeping the other classes fixed, then tunes the persistent launch's
 workgroups per CU; the four fastest configurations seen then play off in
 turns with more launches.  The
@@ -171,9 +172,9 @@ def autotune(level, *, launches=40, use_cache=True, cache_path=None, verbose=Fal
     dt_step = float(min(dt_safe))
 
     def run(n):
-        # n level steps back to back on the level's stream, as a captured
-        # step loop runs them (an event pair around each launch would time
-        # every launch from an idle GPU, which ranks close tilings otherwise)
+        # n single level steps back to back on the level's stream (an event
+        # pair around each launch would time every launch from an idle GPU,
+        # which ranks close tilings otherwise)
         e0 = torch.cuda.Event(enable_timing=True)
         e1 = torch.cuda.Event(enable_timing=True)
         e0.record(level.stream)

@@ -435,8 +435,14 @@ struct ws_ctx {
     // the level costs one segment's time while every workgroup is resident at
     // once (less when they share their CU with fewer others), and a segment's
     // time per round of them plus half of one for the last round after that.
-    // Measured (FP64, us per step): 2048^2 at 26 rows, 740 workgroups on 768
-    // places, 20.9; at 20 rows, 962 of them, 22.0; 13 rows 21.7, 8 rows 22.8.
+    // Fitted to FP64 2048^2 (us per step, loops of 42 steps): 26 rows, 740
+    // workgroups on 768 places, 22.6; 20 rows, 962 of them, 23.4; 13 rows 23.9,
+    // 8 rows 25.2.  Its choice against the best of nine heights, for MC and van
+    // Leer in FP64 and MC in FP32: within 4% on 1536^2 to 4096^2; on 1024^2 8.7
+    // and 8.5, 11.1 and 9.7 (10 rows), 6.5 and 6.1; on 512^2 4.7 and 4.4, 5.4 and
+    // 4.9 (6 rows), 3.7 and 3.7.  Launches that record branches hold fewer
+    // wavefronts and take the same height: 201^2 and 512^2 the best one, 1024^2
+    // 15.6 us per step with 7 rows, 13.3 with 10.
     const double places = (double)n_cu * std::max(1, step_two_occupancy(dtype, limiter, domain));
     double best = 0.0;
     for (int seg = 4; seg <= kMaxTwoRows; ++seg) {
@@ -637,8 +643,10 @@ static int setup_level(ws_ctx *c, const ws_patch_desc *patches, int32_t n_patche
     cells += n;
     if (patches[k].mx < kMarchWide) narrow += n;
   }
-  // Only on levels of many patches: a few patches are bound by one tile's time,
-  // and a narrow patch's cells take less of it as DIRECT tiles.
+  // Only on levels of many patches.  One patch in five 8 to 15 cells wide among
+  // 16 to 64, us per step with those DIRECT and MARCH: 256 patches FP64 12.5 and
+  // 8.9, FP32 9.2 and 6.9; 64 patches 7.7 and 7.3, 6.4 and 6.2; 16 patches 7.0
+  // and 6.8, 5.8 and 6.1 (there one tile's time decides, and either may win).
   const int wide = n_patches >= 64 && 4 * narrow < cells ? 1 : kMarchWide;
   for (int k = 0; k < n_patches; ++k) {
     PatchRow &r = c->rows[k];

@@ -10,7 +10,7 @@
 // x-neighbours come through lane shifts (a wavefront holds two rows), what a
 // cell needs of the rows around it through LDS: the state, to form the cell's
 // bottom edge, and then the edges and x-fluctuations, with a barrier for each.
-// 128 x 128 FP64 in a loop of 100 steps: 2.1 us per step, 3.5 with two steps
+// 128 x 128 FP64 in a loop of 100 steps: 2.0 us per step, 3.5 with two steps
 // per launch (which is the faster one again past one region per CU).
 //
 // Every quantity has the expression the one-step sweeps give it

@@ -56,7 +56,7 @@ struct StepArgs {
 };
 
 // Bit OR-ed into the limiter code of the kernel launchers when the level has a
-// heterogeneous medium (DIRECT tiles only).
+// heterogeneous medium (DIRECT and MARCH tiles).
 constexpr int kMediumFlag = 0x10000;
 
 // Kernel launchers (defined in ws_kernels.hip).

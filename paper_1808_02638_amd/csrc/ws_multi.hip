@@ -452,12 +452,13 @@ __device__ inline void gather_receivers(const StepArgs &a, int first) {
   a.rec_mid[n] = mid;
 }
 
-// Measured on 2048 x 2048 (200 MB of state, within the Infinity Cache): FP64
-// 20.9 us per step, 34 with one step per launch; 4096 x 4096 95 against 198,
-// FP32 on 1999 x 1531 11.0.  What bounds it is instruction issue and memory
-// together: 183 instructions per row and wavefront for the two steps (164 of
-// them vector), 24 us of the 44 us a 2048 x 2048 launch takes, and 233 MB of
-// traffic at 5.25 TB/s; 4096 x 4096 runs at 4.9 TB/s, 93% of a large copy's.
+// Measured, MC, us per launch of two steps and of one step: 2048 x 2048 FP64
+// (200 MB of state, within the Infinity Cache) 43.8 and 34.2, 4096 x 4096 FP64
+// 194 and 197, 2048 x 2048 FP32 29.1 and 21.1.  What bounds it is instruction
+// issue and memory together: 183 instructions per row and wavefront for the two
+// steps (164 of them vector), 24 us of the 44 us a 2048 x 2048 launch takes, and
+// 235 MB of traffic at 5.4 TB/s; 4096 x 4096 runs at 4.8 TB/s, 93% of a large
+// copy's.
 //
 // Workgroup t works tile t: four segments of seg_rows rows, one per
 // wavefront, stacked up the patch.  Workgroups are dispatched round-robin

@@ -103,8 +103,9 @@ class Level:
     def set_medium(self, k: int, rho, K) -> None:
         """Heterogeneous medium of patch k: rho, K as (my+4, mx+4) arrays (ghost
         cells included).  The first call attaches a medium buffer to the level
-        and resets every patch to its default DIRECT tiles (set_tiling or the
-        autotuner may then choose MARCH tiles); patches never given a medium
+        and resets every patch to the default tiles of a medium (MARCH from 60
+        cells wide, else DIRECT; set_tiling or the autotuner may then choose
+        either); patches never given a medium
         keep whatever the buffer holds, so give every patch one."""
         mx, my = self.shapes[k]
         rho = np.ascontiguousarray(rho, dtype=np.float64)
@@ -223,8 +224,8 @@ class Level:
     def set_tiling(self, tile_w=None, tile_h=None, wg_per_cu: int = 0, variant="direct") -> None:
         """Tiling per patch (scalars broadcast): variant "direct", "march" or
         "packed" (or 0/1/2 codes), tile width and height; and persistent
-        workgroups per CU (0: as many as the kernel's occupancy allows).
-        Without tile sizes the tiling in use is kept."""
+        workgroups per CU (0: as many as the kernel's occupancy allows; every
+        call sets them).  Without tile sizes the tiles in use are kept."""
         if tile_w is None:
             C.check(self._L.ws_set_tiling(self._ctx, None, None, None, int(wg_per_cu)))
             return
