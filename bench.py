@@ -44,10 +44,29 @@ RHO, K_BULK = 1.0, 4.0
 C_SOUND = math.sqrt(K_BULK / RHO)
 
 
-def loop_launches(steps):
-    """Launches of a captured loop whose level takes pairs of steps: an even
-    number of pairs, then at least one single step."""
-    return steps - (steps - 1) // 4 * 2
+def loop_launches(torch, shapes, elem_bytes, steps, pairs=True):
+    """Launches of a captured loop of a homogeneous level with extrapolation
+    boundaries: (of two steps, of one), an even number of pairs and then one to
+    four single steps; None for a level of so few 16 x 16 tiles that four steps
+    share a launch.  pairs=False: a level that takes single steps only."""
+    if not pairs:
+        return 0, steps
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    if sum(-(-mx // 16) * -(-my // 16) for mx, my in shapes) <= cus * (2 if elem_bytes == 4 else 1):
+        return None
+    two = (steps - 1) // 4 * 2
+    return two, steps - 2 * two
+
+
+def per_launch(ms, launches, nbytes):
+    """Mean milliseconds of a launch, GB/s and fraction of the HBM peak (every
+    launch, of one step or two, reads and writes the state once); None where the
+    launches are not known."""
+    if launches is None:
+        return None, None, None
+    mean = ms / sum(launches)
+    gbs = nbytes / (mean / 1e3) / 1e9
+    return mean, gbs, round(gbs / HBM_PEAK_GBS, 4)
 
 
 def algorithmic_bytes(shapes, elem_bytes, physical_bc):
@@ -107,8 +126,9 @@ def run_uniform(ws, torch, n, steps, warmup, dtype, kernel_launches, tune=True, 
         from paper_1808_02638_amd.autotune import autotune
         autotune(lev)  # cached per GPU architecture, library build and shape
     var, tw, th, wg, grid = lev.get_tiling()
-    tiling = {"variant": var[0], "tile_w": int(tw[0]), "tile_h": int(th[0]),
-              "wg_per_cu": wg, "grid": grid}
+    # (launches of two steps cut tiles of their own)
+    tiling = {"of": "single steps", "variant": var[0], "tile_w": int(tw[0]),
+              "tile_h": int(th[0]), "wg_per_cu": wg, "grid": grid}
     reset()
     for _ in range(warmup):
         lev.step_auto(0.9)
@@ -137,12 +157,14 @@ def run_uniform(ws, torch, n, steps, warmup, dtype, kernel_launches, tune=True, 
     lev.close()
     return dict(ms=ms, wall_s=wall, sums0=sums0.tolist(), sums1=sums1.tolist(),
                 cfl_last=float(cfl_last[0]), cfl_max=float(cfl_max[0]), finite=finite,
-                launches=steps if transverse_corr else loop_launches(steps), kernel_ms=kernel_ms, tiling=tiling, q=q if keep_state else None)
+                launches=loop_launches(torch, [(n, n)], dtype.itemsize, steps,
+                                       pairs=not transverse_corr),
+                kernel_ms=kernel_ms, tiling=tiling, q=q if keep_state else None)
 
 
 def run_medium(ws, torch, n=2048, steps=200, warmup=10, tune=True):
     """The 2048^2 FP64 pulse in a heterogeneous medium (three layers, +-10%
-    cell perturbation): DIRECT tiles of the variable-coefficient kernel,
+    cell perturbation): tuned tiles of the variable-coefficient kernel,
     CFL 0.9 from the device reduction over the cells, steps in one hipGraph."""
     import numpy as np
 
@@ -195,8 +217,8 @@ def run_medium(ws, torch, n=2048, steps=200, warmup=10, tune=True):
 
 def run_tiled(ws, torch, n=2048, tiles=4, steps=200, warmup=10, tune=True):
     """The 2048^2 FP64 pulse with extrapolating sides cut into tiles x tiles
-    patches that exchange ghosts after every step (a tiled coarsest level);
-    CFL 0.9 from the device reduction, steps in one hipGraph.  Compared with
+    patches that exchange ghosts (a tiled coarsest level); CFL 0.9 with dt
+    updated on the device, steps in one hipGraph.  Compared with
     the single-patch leg this prices the exchange."""
     import numpy as np
 
@@ -363,8 +385,8 @@ def run_ensemble(ws, torch, steps, tune=True):
     nbytes = algorithmic_bytes([(e.mx, e.my) for e in insts], 8, True)
     return {"instances": len(insts), "cells": cells, "steps": steps,
             "bytes_per_step": nbytes,
-            "frac": round(nbytes / (graph_ms / loop_launches(steps) / 1e3) / 1e9
-                          / HBM_PEAK_GBS, 4),
+            "frac": per_launch(graph_ms, loop_launches(torch, [(e.mx, e.my) for e in insts], 8,
+                                                       steps), nbytes)[2],
             "graph_gcells": round(cells * steps / graph_ms / 1e6, 3),
             "eager_gcells": round(cells * steps / eager_ms / 1e6, 3),
             "graph_us_per_step": round(graph_ms * 1e3 / steps, 2),
@@ -461,7 +483,7 @@ def run_adjoint(ws, torch):
                                 "branch_bytes": steps * n * n, "grad_equal": same}}
 
 
-PROFILE = os.path.join(ROOT, "profiles", "step_kernel_march_f64_2048sq.md")
+PROFILE = os.path.join(ROOT, "profiles", "step_kernel_two_f64_f32.md")
 
 
 def run_two_level(ws, torch, steps=20, warmup=3, r=4, n=1024, tune=True):
@@ -592,37 +614,34 @@ def run_three_level(ws, torch, steps=10, warmup=2, r=4, n=512, tune=True):
             "frac": round(nbytes / (ms / 1e3) / 1e9 / HBM_PEAK_GBS, 4), "finite": finite}
 
 
-STEP_KERNEL_SOURCES = ("ws_kernels.hip", "ws_device.h", "ws_internal.h", "ws_tables.h")
+TWO_STEP_SOURCES = ("ws_multi.hip", "ws_device.h", "ws_internal.h", "ws_tables.h", "ws_api.hip")
 
 
-def step_kernel_sha1():
-    """SHA-1 of the step kernel's sources (the kernel file and the three
-    headers it includes from the library), in that order."""
+def two_step_sha1():
+    """SHA-1 of the two-step kernel's sources (the kernel file, the three
+    headers it includes from the library and the host file that cuts its
+    tiles), in that order."""
     import hashlib
 
     h = hashlib.sha1()
-    for name in STEP_KERNEL_SOURCES:
+    for name in TWO_STEP_SOURCES:
         with open(os.path.join(ROOT, "paper_1808_02638_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()
 
 
-def measured_traffic(tiling, profile=PROFILE, n=2048):
-    """HBM bytes per launch of the FP64 step kernel on the n x n grid (2048 or
-    4096) from the committed counter summary, or None when the step kernel's
-    sources have changed since the counters were taken or the tiling differs
-    from the one they were taken with."""
+def measured_traffic(n, profile=PROFILE):
+    """HBM bytes per launch of the FP64 two-step kernel on the n x n grid (2048
+    or 4096) from the committed counter summary, or None for another grid or
+    when the kernel's sources have changed since the counters were taken."""
     try:
         text = open(profile).read()
     except OSError:
         return None
-    sfx = "" if n == 2048 else f"_{n}"
-    keys = ("kernel_source_sha1", f"traffic{sfx}_bytes_per_launch", f"tiling{sfx}")
+    keys = ("kernel_source_sha1", f"traffic_{n}_bytes_per_launch")
     fields = dict(line.split(": ", 1) for line in text.splitlines()
                   if line.split(": ", 1)[0] in keys)
-    if fields.get("kernel_source_sha1", "").strip() != step_kernel_sha1():
-        return None
-    if fields.get(keys[2], "").strip() != f"{tiling['variant']}/{tiling['tile_w']}/{tiling['tile_h']}":
+    if fields.get(keys[0], "").strip() != two_step_sha1():
         return None
     return int(fields[keys[1]]) if keys[1] in fields else None
 
@@ -818,9 +837,9 @@ def main():
             r = run_uniform(ws, torch, nn, kk, args.warmup, dt_, 20, tune=tune)
             eb = 8 if big else 4
             out = {"n": nn, "steps": kk, "value": round(nn * nn * kk / (r["ms"] / 1e3) / 1e9, 3),
-                   "kernel_ms": r["ms"] / kk, "tiling": r["tiling"], "finite": r["finite"],
-                   "frac": round(algorithmic_bytes([(nn, nn)], eb, True)
-                                 / (r["ms"] / r["launches"] / 1e3) / 1e9 / HBM_PEAK_GBS, 4)}
+                   "ms_per_step": r["ms"] / kk, "tiling": r["tiling"], "finite": r["finite"]}
+            out["kernel_ms"], _, out["frac"] = per_launch(
+                r["ms"], r["launches"], algorithmic_bytes([(nn, nn)], eb, True))
         elif args.leg == "amr":
             out = run_amr(ws, torch, torch.float64, args.amr_steps, tune=tune)
         elif args.leg == "ensemble":
@@ -837,10 +856,9 @@ def main():
     bytes64 = algorithmic_bytes(shapes, 8, True)
     # the timed region is launches of the step kernels and nothing else (the
     # Courant numbers and dt updates run inside them): its HIP-event time over
-    # their number is the average launch duration, and every launch, of one
-    # step or two, reads and writes the state once
-    kernel_ms = r64["ms"] / r64["launches"]
-    achieved = bytes64 / (kernel_ms / 1e3) / 1e9
+    # their number is the mean launch duration of the two kernels
+    kernel_ms, achieved, frac = per_launch(r64["ms"], r64["launches"], bytes64)
+    two, one = r64["launches"] or (None, None)
     line = {
         "metric": METRIC,
         "value": round(value, 3),
@@ -860,14 +878,18 @@ def main():
                                f"in one hipGraph",
                    "cells": n * n, "global_batch": 1, "parallelism": "single GPU",
                    "tiling": r64["tiling"]},
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": measured_traffic(r64["tiling"]) if n == 2048 else None,
-                     "kernel": "step_kernel_two<double, MC>",
-                     "launches": r64["launches"],
+        # achieved, frac and kernel_ms: means over all launches of the loop;
+        # traffic: a launch of two steps; kernel_ms_bracketed: a single step
+        "roofline": {"bound": "hbm", "achieved": achieved and round(achieved, 1),
+                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": frac,
+                     "traffic": measured_traffic(n),
+                     "kernel": f"step_kernel_two<double, MC> x {two} and "
+                               f"step_kernel_{r64['tiling']['variant']}<double, MC> x {one}"
+                               if r64["launches"] else "step_kernel_block<double, MC>",
+                     "launches": r64["launches"] and sum(r64["launches"]),
                      "bytes_per_launch": bytes64, "kernel_ms": kernel_ms,
                      "kernel_ms_bracketed": r64["kernel_ms"]},
-        "pct_hbm_peak": round(100 * achieved / HBM_PEAK_GBS, 2),
+        "pct_hbm_peak": frac and round(100 * frac, 2),
         "conservation_fp64": {"start": r64["sums0"], "end": r64["sums1"]},
         "cfl_max": r64["cfl_max"],
         "finite": r64["finite"],
@@ -877,7 +899,7 @@ def main():
         r32 = run_uniform(ws, torch, n, K, args.warmup, torch.float32, args.kernel_launches,
                           tune=not args.no_tune, keep_state=True)
         b32 = algorithmic_bytes(shapes, 4, True)
-        a32 = b32 / (r32["ms"] / r32["launches"] / 1e3) / 1e9
+        k32, a32, f32 = per_launch(r32["ms"], r32["launches"], b32)
         # the FP32 result of the same K steps against the FP64 one (which the
         # tests hold to the FP64 oracle at 1e-12, so this is the FP32 error
         # against the oracle to that accuracy), per component p, u, v
@@ -885,8 +907,8 @@ def main():
         r64["q"] = r32["q"] = None
         line["fp32"] = {"value": round(n * n * K / (r32["ms"] / 1e3) / 1e9, 3),
                         "tiling": r32["tiling"],
-                        "ms_per_step": r32["ms"] / K,
-                        "kernel_GBs": round(a32, 1), "frac": round(a32 / HBM_PEAK_GBS, 4),
+                        "ms_per_step": r32["ms"] / K, "kernel_ms": k32,
+                        "kernel_GBs": a32 and round(a32, 1), "frac": f32,
                         "rel_linf_vs_fp64": [float(f"{e:.3e}") for e in err32],
                         "within_1e-5": bool(max(err32) <= 1e-5), "finite": r32["finite"]}
         # the paper's own limiter, and the variant that also splits the limited
@@ -895,10 +917,10 @@ def main():
                              ("transverse_corr_fp64", "mc", True)):
             rv = run_uniform(ws, torch, n, K, args.warmup, torch.float64, 20,
                              tune=not args.no_tune, limiter=lim, transverse_corr=tc)
-            av = bytes64 / (rv["ms"] / rv["launches"] / 1e3) / 1e9
+            kv, av, fv = per_launch(rv["ms"], rv["launches"], bytes64)
             line[key] = {"value": round(n * n * K / (rv["ms"] / 1e3) / 1e9, 3),
-                         "tiling": rv["tiling"], "kernel_ms": rv["ms"] / K,
-                         "kernel_GBs": round(av, 1), "frac": round(av / HBM_PEAK_GBS, 4),
+                         "tiling": rv["tiling"], "ms_per_step": rv["ms"] / K,
+                         "kernel_ms": kv, "kernel_GBs": av and round(av, 1), "frac": fv,
                          "cfl_max": rv["cfl_max"], "finite": rv["finite"]}
         line["amr_level_batch"] = {
             "fp64": run_amr(ws, torch, torch.float64, args.amr_steps, tune=not args.no_tune),
@@ -908,11 +930,11 @@ def main():
         big = 4096
         rb = run_uniform(ws, torch, big, 100, 5, torch.float64, 20, tune=not args.no_tune)
         bb = algorithmic_bytes([(big, big)], 8, True)
+        kb, _, fb = per_launch(rb["ms"], rb["launches"], bb)
         line["uniform_4096_fp64"] = {
             "value": round(big * big * 100 / (rb["ms"] / 1e3) / 1e9, 3), "steps": 100,
-            "kernel_ms": rb["ms"] / 100,
-            "frac": round(bb / (rb["ms"] / rb["launches"] / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
-            "bytes_per_launch": bb, "traffic": measured_traffic(rb["tiling"], n=big),
+            "ms_per_step": rb["ms"] / 100, "kernel_ms": kb, "frac": fb,
+            "bytes_per_launch": bb, "traffic": measured_traffic(big),
             "tiling": rb["tiling"]}
         line["copy_reference"] = {"pool_size": copy_bandwidth(torch, bytes64 // 2),
                                   "cache_free": copy_bandwidth(torch, 4 * bytes64)}
