@@ -15,8 +15,9 @@ depend on it), so tuning is safe on a live level.
 Choices are cached in a JSON file keyed by GPU architecture, the library's
 step-kernel and tiling sources, dtype, limiter (with the transverse variant)
 and the patch-size histogram.  A table of choices the tuner made on an MI355X for the
-benchmark workloads ships beside this module (``tuned_tilings.json``) and is
-consulted before the user's cache, so a run on a fresh machine uses the same
+benchmark workloads ships beside this module (``tuned_tilings.json``: for each
+workload the fastest of several runs' choices, timed in turns with this
+library's sources) and is consulted before the user's cache, so a run on a fresh machine uses the same
 tilings as the runs its measurements were taken with; ``autotune(...,
 use_cache=False)`` always times the candidates.
 """
